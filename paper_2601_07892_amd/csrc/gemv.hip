@@ -678,6 +678,23 @@ __device__ __forceinline__ int32_t xcd_block(int32_t b, int32_t grid) {
   return x < r ? x * (q + 1) + slot : r * (q + 1) + (x - r) * q + slot;
 }
 
+// A grouped launch too small to fill the GPU runs 2^fold workgroups per
+// prepared block (launch_fold).  Workgroup sub of them takes an equal part of
+// the block's tiles, each split over 2^fold times as many waves (at most
+// kGemvWaves; workgroups that would have no tile left return).
+struct FoldedBlock {
+  int g, S;
+  bool idle;
+  __device__ __forceinline__ FoldedBlock(int block, int sub, int split, int fold) {
+    constexpr int kLogWaves = __builtin_ctz(kGemvWaves);
+    const int room = kLogWaves - __builtin_ctz(split);  // split is a power of two
+    const int f = fold < room ? fold : room;
+    S = split << f;
+    idle = (sub >> f) != 0;
+    g = (block << f) + sub;
+  }
+};
+
 // Barrier for LDS traffic only: outstanding global loads (the weight ring)
 // stay in flight across it.
 __device__ __forceinline__ void lds_barrier() {
@@ -769,11 +786,10 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_tok_kernel(
 }
 
 template <int M, bool kGrp>
-__device__ __forceinline__ void tok_batched_block(const sherry_gemm_desc& d, int g,
+__device__ __forceinline__ void tok_batched_block(const sherry_gemm_desc& d, int g, int S,
                                                   const uint32_t* lut, int8_t* xq) {
   const int k = static_cast<int>(d.k);
   const int kp = ((k + kTileK - 1) / kTileK) * kTileK;
-  const int S = gemv_split((k + kTileK - 1) / kTileK);
   gemv_block<M, kGrp>(d.w, XFromLdsMfmaTok{xq, kp, M}, StageRows<M>{d.x, d.x_scale, k, kp, xq},
                       WScale{d.w_scales, d.w_scale}, d.y, d.acc, d.n, k, g, S, lut,
                       reinterpret_cast<int32_t*>(xq), d.w_group_scales, tok_redf(xq));
@@ -781,11 +797,10 @@ __device__ __forceinline__ void tok_batched_block(const sherry_gemm_desc& d, int
 
 // The same on lane-interleaved weights (per-tensor and per-channel scales).
 template <int M>
-__device__ __forceinline__ void tok_il_batched_block(const sherry_gemm_desc& d, int g,
+__device__ __forceinline__ void tok_il_batched_block(const sherry_gemm_desc& d, int g, int S,
                                                      const uint32_t* lut, int8_t* xq) {
   const int k = static_cast<int>(d.k);
   const int kp = ((k + kTileK - 1) / kTileK) * kTileK;
-  const int S = gemv_split((k + kTileK - 1) / kTileK);
   gemv_block<M>(d.w, XFromLdsMfmaIL{xq, kp, M}, StageRows<M>{d.x, d.x_scale, k, kp, xq},
                 WScale{d.w_scales, d.w_scale}, d.y, d.acc, d.n, k, g, S, lut,
                 reinterpret_cast<int32_t*>(xq));
@@ -794,20 +809,22 @@ __device__ __forceinline__ void tok_il_batched_block(const sherry_gemm_desc& d, 
 // Grouped products of up to four tokens each on lane-interleaved weights
 // (m * ceil(k/128) * 128 <= kTokMaxBytes, no per-group scales).
 __global__ __launch_bounds__(kGemvThreads) void gemv_tok_il_batched_kernel(
-    const sherry_gemm_desc* __restrict__ descs, int count) {
+    const sherry_gemm_desc* __restrict__ descs, int count, int fold) {
   __shared__ uint32_t lut[32];
   __shared__ __attribute__((aligned(16))) int8_t xq[kTokMaxBytes];
   fill_lut(lut);
-  const int32_t blk = static_cast<int32_t>(blockIdx.x);
+  const int32_t blk = static_cast<int32_t>(blockIdx.x) >> fold;
   const int lo = find_block_desc(descs, count, blk);
   if (lo < 0) return;
   const sherry_gemm_desc& d = descs[lo];
-  const int g = blk - d.block_begin;
+  const FoldedBlock fb(blk - d.block_begin, blockIdx.x & ((1 << fold) - 1),
+                       gemv_split((d.k + kTileK - 1) / kTileK), fold);
+  if (fb.idle) return;
   switch (d.m) {
-    case 1: tok_il_batched_block<1>(d, g, lut, xq); break;
-    case 2: tok_il_batched_block<2>(d, g, lut, xq); break;
-    case 3: tok_il_batched_block<3>(d, g, lut, xq); break;
-    default: tok_il_batched_block<4>(d, g, lut, xq); break;
+    case 1: tok_il_batched_block<1>(d, fb.g, fb.S, lut, xq); break;
+    case 2: tok_il_batched_block<2>(d, fb.g, fb.S, lut, xq); break;
+    case 3: tok_il_batched_block<3>(d, fb.g, fb.S, lut, xq); break;
+    default: tok_il_batched_block<4>(d, fb.g, fb.S, lut, xq); break;
   }
 }
 
@@ -817,28 +834,30 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_tok_il_batched_kernel(
 // others keep the registers of the plain stream).
 template <bool kGroups>
 __global__ __launch_bounds__(kGemvThreads) void gemv_tok_batched_kernel(
-    const sherry_gemm_desc* __restrict__ descs, int count) {
+    const sherry_gemm_desc* __restrict__ descs, int count, int fold) {
   __shared__ uint32_t lut[32];
   __shared__ __attribute__((aligned(16))) int8_t xq[kTokMaxBytes];
   fill_lut(lut);
-  const int32_t blk = static_cast<int32_t>(blockIdx.x);
+  const int32_t blk = static_cast<int32_t>(blockIdx.x) >> fold;
   const int lo = find_block_desc(descs, count, blk);
   if (lo < 0) return;
   const sherry_gemm_desc& d = descs[lo];
-  const int g = blk - d.block_begin;
+  const FoldedBlock fb(blk - d.block_begin, blockIdx.x & ((1 << fold) - 1),
+                       gemv_split((d.k + kTileK - 1) / kTileK), fold);
+  if (fb.idle) return;
   if (kGroups && d.w_group_scales) {
     switch (d.m) {
-      case 1: tok_batched_block<1, kGroups>(d, g, lut, xq); break;
-      case 2: tok_batched_block<2, kGroups>(d, g, lut, xq); break;
-      case 3: tok_batched_block<3, kGroups>(d, g, lut, xq); break;
-      default: tok_batched_block<4, kGroups>(d, g, lut, xq); break;
+      case 1: tok_batched_block<1, kGroups>(d, fb.g, fb.S, lut, xq); break;
+      case 2: tok_batched_block<2, kGroups>(d, fb.g, fb.S, lut, xq); break;
+      case 3: tok_batched_block<3, kGroups>(d, fb.g, fb.S, lut, xq); break;
+      default: tok_batched_block<4, kGroups>(d, fb.g, fb.S, lut, xq); break;
     }
   } else {
     switch (d.m) {
-      case 1: tok_batched_block<1, false>(d, g, lut, xq); break;
-      case 2: tok_batched_block<2, false>(d, g, lut, xq); break;
-      case 3: tok_batched_block<3, false>(d, g, lut, xq); break;
-      default: tok_batched_block<4, false>(d, g, lut, xq); break;
+      case 1: tok_batched_block<1, false>(d, fb.g, fb.S, lut, xq); break;
+      case 2: tok_batched_block<2, false>(d, fb.g, fb.S, lut, xq); break;
+      case 3: tok_batched_block<3, false>(d, fb.g, fb.S, lut, xq); break;
+      default: tok_batched_block<4, false>(d, fb.g, fb.S, lut, xq); break;
     }
   }
 }
@@ -873,12 +892,13 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_group_kernel(
 }
 
 __global__ __launch_bounds__(kGemvThreads) void gemv_batched_kernel(
-    const sherry_gemv_desc* __restrict__ descs, int count) {
+    const sherry_gemv_desc* __restrict__ descs, int count, int fold) {
   __shared__ uint32_t lut[32];
   __shared__ int32_t red[kGemvWaves * 64];
   __shared__ float redf[kGemvWaves * 64];
   fill_lut(lut);
-  const int32_t blk = xcd_block(static_cast<int32_t>(blockIdx.x), static_cast<int32_t>(gridDim.x));
+  const int32_t xb = xcd_block(static_cast<int32_t>(blockIdx.x), static_cast<int32_t>(gridDim.x));
+  const int32_t blk = xb >> fold;
   // last descriptor with block_begin <= blk: block_begin strictly increases,
   // so the descriptors that qualify form a prefix; each lane tests one
   // descriptor and the prefix length comes from a ballot (one load round
@@ -896,14 +916,16 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_batched_kernel(
   lo = __builtin_amdgcn_readfirstlane(lo);
   const sherry_gemv_desc& d = descs[lo];
   const int k = static_cast<int>(d.k);
-  const int S = gemv_split(static_cast<int>((k + kTileK - 1) / kTileK));
+  const FoldedBlock fb(blk - d.block_begin, xb & ((1 << fold) - 1),
+                       gemv_split(static_cast<int>((k + kTileK - 1) / kTileK)), fold);
+  if (fb.idle) return;
   const XFromSgpr<1> xs{as_const(reinterpret_cast<const int32_t*>(d.x)), k};
   if (d.w_group_scales) {
     gemv_block<1, true>(d.w, xs, ReadScales<1>{d.x_scale}, WScale{nullptr, 0.0f}, d.y, d.acc,
-                        d.n, k, blk - d.block_begin, S, lut, red, d.w_group_scales, redf);
+                        d.n, k, fb.g, fb.S, lut, red, d.w_group_scales, redf);
   } else {
     gemv_block<1>(d.w, xs, ReadScales<1>{d.x_scale}, WScale{d.w_scales, d.w_scale}, d.y, d.acc,
-                  d.n, k, blk - d.block_begin, S, lut, red);
+                  d.n, k, fb.g, fb.S, lut, red);
   }
 }
 
@@ -1053,14 +1075,15 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_f32_group_kernel(
 
 template <bool kIL>
 __global__ __launch_bounds__(kGemvThreads) void gemv_f32_batched_kernel(
-    const sherry_gemv_f32_desc* __restrict__ descs, int count) {
+    const sherry_gemv_f32_desc* __restrict__ descs, int count, int fold) {
   __shared__ uint32_t lut[32];
   __shared__ int32_t red[kGemvWaves * 64];
   __shared__ float redf[kGemvWaves * 64];
   __shared__ float part[kGemvWaves];
   __shared__ __attribute__((aligned(16))) int8_t xq[kFusedMaxK];
   fill_lut(lut);
-  const int32_t blk = xcd_block(static_cast<int32_t>(blockIdx.x), static_cast<int32_t>(gridDim.x));
+  const int32_t xb = xcd_block(static_cast<int32_t>(blockIdx.x), static_cast<int32_t>(gridDim.x));
+  const int32_t blk = xb >> fold;
   const int lane = threadIdx.x & 63;
   int lo = 0;
   for (int base = 0; base < count; base += 64) {
@@ -1075,18 +1098,18 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_f32_batched_kernel(
   const sherry_gemv_f32_desc& d = descs[lo];
   const int k = static_cast<int>(d.k);
   const int C = (k + kTileK - 1) / kTileK;
-  const int S = fused_split(C);
+  const FoldedBlock fb(blk - d.block_begin, xb & ((1 << fold) - 1), fused_split(C), fold);
+  if (fb.idle) return;
+  const bool first = fb.g == 0;
   if constexpr (kIL) {
-    fused_block<false, true>(d.w, d.x, d.x_scale, blk == d.block_begin,
-                             WScale{d.w_scales, d.w_scale}, d.y, d.acc, d.n, k,
-                             blk - d.block_begin, S, lut, red, part, xq);
+    fused_block<false, true>(d.w, d.x, d.x_scale, first, WScale{d.w_scales, d.w_scale}, d.y,
+                             d.acc, d.n, k, fb.g, fb.S, lut, red, part, xq);
   } else if (d.w_group_scales) {
-    fused_block<true>(d.w, d.x, d.x_scale, blk == d.block_begin, WScale{nullptr, 0.0f}, d.y,
-                      d.acc, d.n, k, blk - d.block_begin, S, lut, red, part, xq,
-                      d.w_group_scales, redf);
+    fused_block<true>(d.w, d.x, d.x_scale, first, WScale{nullptr, 0.0f}, d.y, d.acc, d.n, k,
+                      fb.g, fb.S, lut, red, part, xq, d.w_group_scales, redf);
   } else {
-    fused_block(d.w, d.x, d.x_scale, blk == d.block_begin, WScale{d.w_scales, d.w_scale}, d.y,
-                d.acc, d.n, k, blk - d.block_begin, S, lut, red, part, xq);
+    fused_block(d.w, d.x, d.x_scale, first, WScale{d.w_scales, d.w_scale}, d.y, d.acc, d.n, k,
+                fb.g, fb.S, lut, red, part, xq);
   }
 }
 
@@ -1139,6 +1162,23 @@ int launch_gemv_tok(const uint8_t* w, const int8_t* x, const float* x_scale, WSc
   }
 }
 
+// Workgroups per prepared block of a grouped launch, as a power of two.  The
+// prepared blocks keep up to 16 units (32 in the fused step) in one wave,
+// which is best for a launch that fills the GPU; a launch that does not takes
+// as long as one such wave, and is bound by that chain.  Spread over up to one
+// workgroup per CU, the four launches of a LLaMA-3.2-3B layer at one token
+// take 26.9 us instead of 55.5 (LLaMA-3.2-1B 24.4 / 43.8, 8B-scale 34.3 /
+// 57.6; 3B at 4 tokens with per-group scales 47.7 / 57.5).  Past one
+// workgroup per CU it does not pay: two 1B layers in one launch (29 blocks)
+// 13.4 us as prepared, 10.3 in 232 workgroups, 12.8 in 464, 18.8 in 928, since
+// every workgroup stages its activation rows again.
+constexpr int64_t kFoldBlocks = 256;
+int launch_fold(int64_t total_blocks) {
+  int fold = 0;
+  while (fold < 3 && (total_blocks << (fold + 1)) <= kFoldBlocks) ++fold;
+  return fold;
+}
+
 int64_t gemv_tok_blocks(int64_t n, int64_t k) {
   return ceil_div(ceil_div(n, kTileRows) * gemv_split(static_cast<int>(ceil_div(k, kTileK))),
                   kGemvWaves);
@@ -1146,17 +1186,17 @@ int64_t gemv_tok_blocks(int64_t n, int64_t k) {
 
 int launch_gemv_tok_il_batched(const sherry_gemm_desc* descs, int count, int64_t total_blocks,
                                hipStream_t s) {
-  return launch(gemv_tok_il_batched_kernel, dim3(static_cast<unsigned>(total_blocks)),
-                dim3(kGemvThreads), 0, s, descs, count);
+  const int fold = launch_fold(total_blocks);
+  return launch(gemv_tok_il_batched_kernel, dim3(static_cast<unsigned>(total_blocks << fold)),
+                dim3(kGemvThreads), 0, s, descs, count, fold);
 }
 
 int launch_gemv_tok_batched(const sherry_gemm_desc* descs, int count, int64_t total_blocks,
                             bool groups, hipStream_t s) {
-  if (groups)
-    return launch(gemv_tok_batched_kernel<true>, dim3(static_cast<unsigned>(total_blocks)),
-                  dim3(kGemvThreads), 0, s, descs, count);
-  return launch(gemv_tok_batched_kernel<false>, dim3(static_cast<unsigned>(total_blocks)),
-                dim3(kGemvThreads), 0, s, descs, count);
+  const int fold = launch_fold(total_blocks);
+  const dim3 grid(static_cast<unsigned>(total_blocks << fold)), block(kGemvThreads);
+  if (groups) return launch(gemv_tok_batched_kernel<true>, grid, block, 0, s, descs, count, fold);
+  return launch(gemv_tok_batched_kernel<false>, grid, block, 0, s, descs, count, fold);
 }
 
 int launch_gemv_group(const uint8_t* w, const int8_t* x, const float* x_scale, const float* gs,
@@ -1186,8 +1226,9 @@ int launch_gemv_f32_group(const uint8_t* w, const float* x, float* x_scale, cons
 
 int launch_gemv_batched(const sherry_gemv_desc* descs, int count, int64_t total_blocks,
                         hipStream_t s) {
-  return launch(gemv_batched_kernel, dim3(static_cast<unsigned>(total_blocks)),
-                dim3(kGemvThreads), 0, s, descs, count);
+  const int fold = launch_fold(total_blocks);
+  return launch(gemv_batched_kernel, dim3(static_cast<unsigned>(total_blocks << fold)),
+                dim3(kGemvThreads), 0, s, descs, count, fold);
 }
 
 int launch_gemv_f32(const uint8_t* w, const float* x, float* x_scale, WScale ws, float* y,
@@ -1201,11 +1242,10 @@ int launch_gemv_f32(const uint8_t* w, const float* x, float* x_scale, WScale ws,
 
 int launch_gemv_f32_batched(const sherry_gemv_f32_desc* descs, int count, int64_t total_blocks,
                             bool il, hipStream_t s) {
-  if (il)
-    return launch(gemv_f32_batched_kernel<true>, dim3(static_cast<unsigned>(total_blocks)),
-                  dim3(kGemvThreads), 0, s, descs, count);
-  return launch(gemv_f32_batched_kernel<false>, dim3(static_cast<unsigned>(total_blocks)),
-                dim3(kGemvThreads), 0, s, descs, count);
+  const int fold = launch_fold(total_blocks);
+  const dim3 grid(static_cast<unsigned>(total_blocks << fold)), block(kGemvThreads);
+  if (il) return launch(gemv_f32_batched_kernel<true>, grid, block, 0, s, descs, count, fold);
+  return launch(gemv_f32_batched_kernel<false>, grid, block, 0, s, descs, count, fold);
 }
 
 }  // namespace sherry
