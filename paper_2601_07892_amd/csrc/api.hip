@@ -43,10 +43,8 @@ int check_fused(const uint8_t* w, const float* x, const float* x_scale, float* y
 // the register-decoded MFMA kernel (LLaMA-3.2-3B and 8B-scale projections,
 // single launches).
 constexpr int64_t kGemvMaxM = 4;
-// The register-decoded MFMA kernel takes every product of up to
-// kSkinnyMaxLongM tokens and every product with k > n or k >= kSkinnyMinLongK;
-// the LDS-tiled kernel keeps the longer products with k <= 2048 <= n (about
-// 5% faster on those shapes at 16384 tokens).
+// Shape classes of sherry_gemm_kernel_for past that: products of up to
+// kSkinnyMaxLongM tokens, with k > n or with k >= kSkinnyMinLongK, and the rest.
 constexpr int64_t kSkinnyMinLongK = 3072, kSkinnyMaxLongM = 8192;
 
 int check_product(const uint8_t* w, const int8_t* x, const float* x_scale, float* y,
@@ -120,9 +118,6 @@ extern "C" int sherry_quantize_act_batched(const sherry_quant_desc* descs_dev, i
 extern "C" int sherry_gemm_kernel_for(int64_t m, int64_t n, int64_t k) {
   if (!shape_ok(m, n, k)) return -SHERRY_E_SHAPE;
   if (m <= kGemvMaxM) return SHERRY_KERNEL_GEMV;
-  // measured: the register-decoded kernel is as fast or faster on every
-  // LLaMA shape up to 8192 tokens and on every k >= 3072 shape; the LDS-tiled
-  // kernel keeps the longer, k <= 2048 products (5% faster at 16384 tokens)
   const bool skinny = m <= kSkinnyMaxLongM || k > n || k >= kSkinnyMinLongK;
   return skinny ? SHERRY_KERNEL_SKINNY : SHERRY_KERNEL_MFMA;
 }
@@ -138,7 +133,10 @@ int gemm_dispatch(const uint8_t* w, const int8_t* x, const float* x_scale, WScal
                   int32_t* acc, int64_t m, int64_t n, int64_t k, int kernel, void* stream) {
   if (kernel == SHERRY_KERNEL_AUTO) {
     const int kk = sherry_gemm_kernel_for(m, n, k);
-    kernel = kk < 0 ? SHERRY_KERNEL_GEMV : kk;
+    // the register-decoded kernel's 128-token workgroups also serve the longer
+    // products that sherry_gemm_kernel_for sets apart (16384 x 8192 x 2048: 301
+    // us, LDS-tiled 349; 16384 x 2048 x 2048: 85, 86)
+    kernel = kk < 0 ? SHERRY_KERNEL_GEMV : m > kGemvMaxM ? SHERRY_KERNEL_SKINNY : kk;
   }
   if (kernel == SHERRY_KERNEL_GEMV) {
     int st = check_product(w, x, x_scale, y, m, n, k, 4);
@@ -151,7 +149,8 @@ int gemm_dispatch(const uint8_t* w, const int8_t* x, const float* x_scale, WScal
     int st = check_product(w, x, x_scale, y, m, n, k, 16);
     if (st != SHERRY_OK) return st;
     if (acc && !aligned(acc, 4)) return SHERRY_E_ALIGN;
-    return launch_skinny(w, x, x_scale, ws, y, acc, m, n, k, as_stream(stream));
+    return launch_wide(w, x, x_scale, ws, y, acc, m, n, k, as_stream(stream));
+    return launch_wide(w, x, x_scale, ws, y, acc, m, n, k, as_stream(stream));
   }
   if (kernel == SHERRY_KERNEL_MFMA) {
     int st = check_product(w, x, x_scale, y, m, n, k, 16);

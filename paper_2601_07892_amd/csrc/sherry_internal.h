@@ -265,10 +265,14 @@ int64_t smallm_blocks(int64_t n);
 int launch_smallm_batched(const sherry_gemm_desc* descs, int count, int64_t total_blocks,
                           bool groups, hipStream_t s);
 
+// Register-decoded MFMA product of any m (wide.hip), per-tensor or per-channel
+// scales: lone, and grouped in the prepared blocks of 8 tiles x 64 tokens.
+int launch_wide(const uint8_t* w, const int8_t* x, const float* x_scale, WScale ws, float* y,
+                int32_t* acc, int64_t m, int64_t n, int64_t k, hipStream_t s);
+int launch_wide_batched(const sherry_gemm_desc* descs, int count, int64_t total_blocks,
+                        int max_m, hipStream_t s);
 int skinny_blocks(int64_t n, bool group_scales = false);
 int skinny_batched_tokens(int max_m);
-int launch_skinny(const uint8_t* w, const int8_t* x, const float* x_scale, WScale ws,
-                  float* y, int32_t* acc, int64_t m, int64_t n, int64_t k, hipStream_t s);
 int launch_skinny_batched(const sherry_gemm_desc* descs, int count, int64_t total_blocks,
                           int max_m, hipStream_t s);
 int launch_gemv_batched(const sherry_gemv_desc* descs, int count,

@@ -681,21 +681,13 @@ int launch_skinny_mt(const SkProblem& p, hipStream_t s) {
   }
 }
 
-int launch_skinny(const uint8_t* w, const int8_t* x, const float* x_scale, WScale ws,
-                  float* y, int32_t* acc, int64_t m, int64_t n, int64_t k, hipStream_t s) {
-  const SkProblem p{w, x, x_scale, y, acc, static_cast<int>(n), static_cast<int>(k),
-                    static_cast<int>(m), ws, nullptr};
-  if (m <= 32) return launch_skinny_mt<1>(p, s);
-  return launch_skinny_mt<2>(p, s);
-}
-
 // Per-group scales: 32-token blocks for every M (the fp32 sums and int32
 // totals double the accumulator registers).
 int launch_skinny_group(const uint8_t* w, const int8_t* x, const float* x_scale, const float* gs,
                         float* y, int32_t* acc, int64_t m, int64_t n, int64_t k, hipStream_t s) {
   if (acc) {
     // int32 totals from an unscaled launch (its y is overwritten below)
-    const int rc = launch_skinny(w, x, x_scale, WScale{nullptr, 1.0f}, y, acc, m, n, k, s);
+    const int rc = launch_wide(w, x, x_scale, WScale{nullptr, 1.0f}, y, acc, m, n, k, s);
     if (rc != SHERRY_OK) return rc;
   }
   const SkProblem p{w, x, x_scale, y, nullptr, static_cast<int>(n), static_cast<int>(k),
@@ -705,9 +697,9 @@ int launch_skinny_group(const uint8_t* w, const int8_t* x, const float* x_scale,
 
 int launch_skinny_batched(const sherry_gemm_desc* descs, int count, int64_t total_blocks,
                           int max_m, hipStream_t s) {
+  if (max_m > 32) return launch_wide_batched(descs, count, total_blocks, max_m, s);
   const dim3 grid(static_cast<unsigned>(total_blocks)), block(64 * kSkWavesGrouped);
-  if (max_m <= 32) return launch(skinny_batched_kernel<1>, grid, block, 0, s, descs, count);
-  return launch(skinny_batched_kernel<2>, grid, block, 0, s, descs, count);
+  return launch(skinny_batched_kernel<1>, grid, block, 0, s, descs, count);
 }
 
 }  // namespace sherry
