@@ -207,8 +207,7 @@ extern "C" int sherry_gemm_group(const uint8_t* w, const int8_t* x, const float*
     int st = check_product(w, x, x_scale, y, m, n, k, 16);
     if (st != SHERRY_OK) return st;
     if (acc && !aligned(acc, 4)) return SHERRY_E_ALIGN;
-    return launch_skinny_group(w, x, x_scale, w_group_scales, y, acc, m, n, k,
-                               as_stream(stream));
+    return launch_wide_group(w, x, x_scale, w_group_scales, y, acc, m, n, k, as_stream(stream));
   }
   if (kernel == SHERRY_KERNEL_MFMA) {
     int st = check_product(w, x, x_scale, y, m, n, k, 16);
@@ -491,9 +490,9 @@ extern "C" int sherry_gemm_batched_prepare(sherry_gemm_desc* descs, int count,
   // blocks of the size the largest m selects (per-group scales: 32-token
   // blocks)
   const int32_t sel = grouped && mm > 32 ? 32 : (mm < 17 ? 17 : mm);
-  const int64_t tokens = skinny_batched_tokens(sel);
+  const int64_t tokens = wide_batched_tokens(sel);
   const int st = assign_blocks(descs, count, [&](const sherry_gemm_desc& d) {
-    return int64_t(skinny_blocks(d.n, d.w_group_scales != nullptr)) * ceil_div(d.m, tokens);
+    return int64_t(wide_blocks(d.n, d.w_group_scales != nullptr)) * ceil_div(d.m, tokens);
   }, total_blocks);
   if (st != SHERRY_OK) return st;
   *max_m = sel | (grouped ? SHERRY_LAUNCH_GROUPS : 0);
@@ -548,7 +547,7 @@ extern "C" int sherry_gemm_batched(const sherry_gemm_desc* descs_dev, int count,
     return launch_gemv_tok_batched(descs_dev, count, total_blocks, groups, as_stream(stream));
   if (max_m <= 16)
     return launch_smallm_batched(descs_dev, count, total_blocks, groups, as_stream(stream));
-  return launch_skinny_batched(descs_dev, count, total_blocks, max_m, as_stream(stream));
+  return launch_wide_batched(descs_dev, count, total_blocks, max_m, groups, as_stream(stream));
 }
 
 extern "C" int sherry_ternarize_pack(const float* w, int64_t n, int64_t k, uint8_t* packed,

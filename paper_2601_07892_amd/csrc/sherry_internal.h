@@ -265,16 +265,17 @@ int64_t smallm_blocks(int64_t n);
 int launch_smallm_batched(const sherry_gemm_desc* descs, int count, int64_t total_blocks,
                           bool groups, hipStream_t s);
 
-// Register-decoded MFMA product of any m (wide.hip), per-tensor or per-channel
-// scales: lone, and grouped in the prepared blocks of 8 tiles x 64 tokens.
+// Register-decoded MFMA product of any m (wide.hip), per-tensor, per-channel or
+// per-group scales: lone, and grouped in wide_blocks(n) tile groups x blocks of
+// wide_batched_tokens(max_m) tokens.
 int launch_wide(const uint8_t* w, const int8_t* x, const float* x_scale, WScale ws, float* y,
                 int32_t* acc, int64_t m, int64_t n, int64_t k, hipStream_t s);
+int launch_wide_group(const uint8_t* w, const int8_t* x, const float* x_scale, const float* gs,
+                      float* y, int32_t* acc, int64_t m, int64_t n, int64_t k, hipStream_t s);
+int wide_blocks(int64_t n, bool group_scales);
+int wide_batched_tokens(int max_m);
 int launch_wide_batched(const sherry_gemm_desc* descs, int count, int64_t total_blocks,
-                        int max_m, hipStream_t s);
-int skinny_blocks(int64_t n, bool group_scales = false);
-int skinny_batched_tokens(int max_m);
-int launch_skinny_batched(const sherry_gemm_desc* descs, int count, int64_t total_blocks,
-                          int max_m, hipStream_t s);
+                        int max_m, bool groups, hipStream_t s);
 int launch_gemv_batched(const sherry_gemv_desc* descs, int count,
                         int64_t total_blocks, hipStream_t s);
 int launch_gemv_f32(const uint8_t* w, const float* x, float* x_scale, WScale ws, float* y,
@@ -288,8 +289,6 @@ int launch_gemv_group(const uint8_t* w, const int8_t* x, const float* x_scale, c
                       float* y, int32_t* acc, int64_t m, int64_t n, int64_t k, hipStream_t s);
 int launch_gemv_f32_group(const uint8_t* w, const float* x, float* x_scale, const float* gs,
                           float* y, int32_t* acc, int64_t n, int64_t k, hipStream_t s);
-int launch_skinny_group(const uint8_t* w, const int8_t* x, const float* x_scale, const float* gs,
-                        float* y, int32_t* acc, int64_t m, int64_t n, int64_t k, hipStream_t s);
 
 // MFMA tile configuration chosen for an m x n product: 0 skinny (32 x 256),
 // 1 small (128 x 128), 2 mid (128 x 256), 3 large (256 x 256).

@@ -1,5 +1,6 @@
 // Register-decoded int8-MFMA product (Eq. 2): every lone product of five and
-// more tokens, and the grouped launches of more than 32.
+// more tokens, and the grouped launches of more than 16 (with per-group scales
+// whose rows the window kernel does not take, of more than four).
 //
 // Work mapping.  A wave owns one 64-row tile (or one of S parts of its K) and
 // 32 MT tokens; a workgroup is W waves, W / S tiles.  Per container (64 rows x
@@ -31,6 +32,8 @@
 // stages changed nothing) and by about 5 us of launch, first loads, reduction
 // and stores.  They run smaller workgroups with K split over more waves, as
 // the cost model below picks.
+#include <type_traits>
+
 #include "sherry_internal.h"
 
 namespace sherry {
@@ -48,9 +51,14 @@ constexpr int kWdSW = 40;                  // words per token of an epilogue str
 // register budget).  RING weight containers per wave in registers; NST stages
 // of one container's activations in LDS: the S parts' windows as S x TOK
 // virtual rows of 128 bytes.
-template <int MT_, int S_, int W_, int EU_>
+//
+// GR: per-group weight scales, one per row and 128 weights, i.e. per unit:
+// 1 with a 4-byte load per lane and unit (any row length), 4 with a 16-byte
+// load per lane and four units (rows of whole, aligned 16-byte pieces; a
+// quarter of the cache lines touched).
+template <int MT_, int S_, int W_, int EU_, int GR_ = 0>
 struct WdCfg {
-  static constexpr int MT = MT_, S = S_, W = W_, EU = EU_, RING = 4, NST = 4;
+  static constexpr int MT = MT_, S = S_, W = W_, EU = EU_, GR = GR_, RING = 4, NST = 4;
   static_assert(RING % NST == 0, "ring slots and stages repeat together");
   static constexpr int THREADS = 64 * W;
   static constexpr int TOK = 32 * MT;
@@ -81,6 +89,7 @@ struct WdProblem {
   int32_t* acc;
   int n, k, m;
   WScale ws;
+  const float* gs;  // per-group scales [n][ceil(k/128)]
 };
 
 // Waits until at most N vector-memory loads of this wave are outstanding
@@ -92,18 +101,6 @@ __device__ __forceinline__ void wd_wait_vm() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   constexpr int kImm = (N & 15) | (7 << 4) | (15 << 8) | (((N >> 4) & 3) << 14);
   __builtin_amdgcn_s_waitcnt(static_cast<int16_t>(kImm));
-}
-// N + 2u outstanding loads (u a constant once unrolled)
-template <int N>
-__device__ __forceinline__ void wd_wait_first(int u) {
-  switch (u) {
-    case 0: wd_wait_vm<wd_cap(N)>(); break;
-    case 1: wd_wait_vm<wd_cap(N + 2)>(); break;
-    case 2: wd_wait_vm<wd_cap(N + 4)>(); break;
-    case 3: wd_wait_vm<wd_cap(N + 6)>(); break;
-    case 4: wd_wait_vm<wd_cap(N + 8)>(); break;
-    default: wd_wait_vm<wd_cap(N + 10)>(); break;
-  }
 }
 // Waits for this wave's LDS reads and writes.
 __device__ __forceinline__ void wd_wait_lgkm() {
@@ -177,7 +174,8 @@ __device__ __forceinline__ void wd_interleave() {
 // One slice: the MFMAs of group s; on the way the lookups of group l of the
 // container in d, the fragments of the next slice (xn from pn) and the swap
 // of the next slice's group.
-template <int MT, int s, int l>
+// With kZero the sums start from zero.
+template <int MT, int s, int l, bool kZero = false>
 __device__ __forceinline__ void wd_slice(uint32_t (&wv)[32], const uint32_t (&d)[5],
                                          const uint32_t* lut, const v4i (&xv)[MT], v4i (&xn)[MT],
                                          const int8_t* pn, v16i (&c)[2][MT]) {
@@ -191,8 +189,8 @@ __device__ __forceinline__ void wd_slice(uint32_t (&wv)[32], const uint32_t (&d)
   wd_lookup8<8 * l>(d, lut, wv, std::make_integer_sequence<int, 8>{});
 #pragma unroll
   for (int tb = 0; tb < MT; ++tb) {
-    c[0][tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xv[tb], wl, c[0][tb], 0, 0, 0);
-    c[1][tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xv[tb], wh, c[1][tb], 0, 0, 0);
+    c[0][tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xv[tb], wl, kZero ? v16i{} : c[0][tb], 0, 0, 0);
+    c[1][tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xv[tb], wh, kZero ? v16i{} : c[1][tb], 0, 0, 0);
   }
   wd_interleave<2 * MT>();
   __builtin_amdgcn_sched_barrier(0);
@@ -223,7 +221,8 @@ __device__ __forceinline__ void wd_block(const WdProblem& p, int g, int8_t* lds)
   int8_t* const xs = lds + kWdHead;
   const int C = (p.k + kTileK - 1) / kTileK;
   const int R = (p.n + kTileRows - 1) / kTileRows;
-  const int U = (C + S - 1) / S;
+  // (with 16-byte scale loads the parts are whole chunks of four units)
+  const int U = G::GR == 4 ? ((C + S - 1) / S + 3) & ~3 : (C + S - 1) / S;
   const int r = g * G::TILES + wave / S;
   const int sp = wave % S;
   const int u0 = sp * U, u1 = (u0 + U < C) ? u0 + U : C;
@@ -283,13 +282,37 @@ __device__ __forceinline__ void wd_block(const WdProblem& p, int g, int8_t* lds)
 #pragma unroll
     for (int tb = 0; tb < MT; ++tb) c[h][tb] = v16i{};
 
+  // per-group: fp32 sums in unit order, and the scales of this lane's row
+  // (lane i = row i of the tile; rows past n and units past the part read
+  // zeros): slot u of gq holds the unit in flight at position u, the next
+  // four come in while these are used
+  typedef float v16f __attribute__((ext_vector_type(16)));
+  constexpr int GM = G::GR ? MT : 1;
+  v16f cf[2][GM];
+  uint32_t gq[4];
+  u32x4 gn;
+  __amdgpu_buffer_rsrc_t grs;
+  if constexpr (G::GR != 0) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int tb = 0; tb < MT; ++tb) cf[h][tb] = v16f{};
+    const int rows = r < R ? p.n - r * kTileRows : 0;
+    grs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(p.gs) + int64_t(r < R ? r : 0) * kTileRows * C, 0,
+        (rows < kTileRows ? rows : kTileRows) * C * 4, kBufferWord3);
+  }
+  auto scale_off = [&](int unit) {
+    return unit < u1 - u0 ? 4 * (lane * C + u0 + unit) : kWdOutside;
+  };
+
   // the epilogue's scales, through LDS: loaded before anything else, since a
   // load between the stores would wait for every store before it
   float sxv = 0.0f, swv = 0.0f;
   if (tid < G::TOK) sxv = tid < p.m ? as_global(p.x_scale)[tid] : 0.0f;
   {
     const int row = g * G::TILES * kTileRows + tid;
-    if (tid < G::TILES * kTileRows) swv = row < p.n ? p.ws.at(row) : 0.0f;
+    if (!G::GR && tid < G::TILES * kTileRows) swv = row < p.n ? p.ws.at(row) : 0.0f;
   }
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -303,10 +326,22 @@ __device__ __forceinline__ void wd_block(const WdProblem& p, int g, int8_t* lds)
     load_unit(ring[u], rs, u, lane);
     __builtin_amdgcn_sched_barrier(0);
   }
+  if constexpr (G::GR == 4) {
+    const u32x4 g0 = __builtin_amdgcn_raw_buffer_load_b128(grs, scale_off(0), 0, 0);
+    gn = __builtin_amdgcn_raw_buffer_load_b128(grs, scale_off(4), 0, 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) gq[e] = g0[e];
+  } else if constexpr (G::GR == 1) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      gq[e] = __builtin_amdgcn_raw_buffer_load_b32(grs, scale_off(e), 0, 0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  constexpr int GP = G::GR == 4 ? 2 : G::GR == 1 ? 4 : 0;  // scale loads of the prologue
   if (tid < 32) lut[tid] = decode_word(tid);
   if (tid < G::TOK) xsl[tid] = sxv;
-  if (tid < G::TILES * kTileRows) wsl[tid] = swv;
-  wd_wait_vm<wd_cap((D - 1) * G::SPT + 2 * G::RING)>();
+  if (!G::GR && tid < G::TILES * kTileRows) wsl[tid] = swv;
+  wd_wait_vm<wd_cap((D - 1) * G::SPT + 2 * G::RING + GP)>();
   wd_wait_lgkm();
   wd_barrier();  // chunk 0, the table and the scales are ready
   if (chl == 0) clear_tail();
@@ -329,13 +364,23 @@ __device__ __forceinline__ void wd_block(const WdProblem& p, int g, int8_t* lds)
       const uint32_t (&dn)[5] = ring[(u + 1) % G::RING];
       const int8_t* st = xs + u % G::NST * G::STAGE;
       const int8_t* sn = xs + (u + 1) % G::NST * G::STAGE;
-      wd_slice<MT, 0, 3>(wv, ring[u], lut, xv[0], xv[XD % XN], st + lo[XD], c);
+      wd_slice<MT, 0, 3, G::GR != 0>(wv, ring[u], lut, xv[0], xv[XD % XN], st + lo[XD], c);
       load_unit(ring[u], rs, jj + G::RING, lane);
       wd_slice<MT, 1, 0>(wv, dn, lut, xv[1], xv[(1 + XD) % XN], st + lo[1 + XD], c);
       // chunk jj + 1 has landed for every wave after this barrier, and every
       // wave is done with the stage of chunk jj - 1
-      if (u < D - 1 && j == 0) wd_wait_first<(D - 2) * G::SPT + 2 * G::RING + 2>(u);
-      else wd_wait_vm<wd_cap(2 * (D - 1) + (D - 2) * G::SPT)>();
+      // (scale loads go out at the end of a unit: of every one, or, four units'
+      // at once, of the last in a round)
+      constexpr int LU = G::GR == 1 ? 3 : 2;  // loads per unit besides the DMA
+      const int ge = G::GR == 4 && u < 2 ? 1 : 0;
+      if (u < D - 1 && j == 0) {
+        if (u == 0) wd_wait_vm<wd_cap((D - 2) * G::SPT + 2 * G::RING + GP + 2)>();
+        else wd_wait_vm<wd_cap((D - 2) * G::SPT + 2 * G::RING + GP + 2 + LU)>();
+      } else if (ge) {
+        wd_wait_vm<wd_cap(LU * (D - 1) + (D - 2) * G::SPT + 1)>();
+      } else {
+        wd_wait_vm<wd_cap(LU * (D - 1) + (D - 2) * G::SPT)>();
+      }
       wd_barrier();
       if (jj + 1 == chl) clear_tail();
 #pragma unroll
@@ -343,6 +388,27 @@ __device__ __forceinline__ void wd_block(const WdProblem& p, int g, int8_t* lds)
       wd_slice<MT, 2, 1>(wv, dn, lut, xv[2 % XN], xv[(2 + XD) % XN],
                          XD == 2 ? sn + lo[0] : st + lo[3], c);
       wd_slice<MT, 3, 2>(wv, dn, lut, xv[3 % XN], xv[(3 + XD) % XN], sn + lo[XD - 1], c);
+      if constexpr (G::GR != 0) {
+        // rows lane % 32 and lane % 32 + 32
+        const auto gr = __builtin_amdgcn_permlane32_swap(gq[u], gq[u], false, false);
+#pragma unroll
+        for (int tb = 0; tb < MT; ++tb)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const float sc = __uint_as_float(h ? gr[1] : gr[0]);
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+              cf[h][tb][e] = __builtin_fmaf(static_cast<float>(c[h][tb][e]), sc, cf[h][tb][e]);
+          }
+        if constexpr (G::GR == 1) {
+          gq[u] = __builtin_amdgcn_raw_buffer_load_b32(grs, scale_off(jj + 4), 0, 0);
+        } else if (u == 3) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) gq[e] = gn[e];
+          gn = __builtin_amdgcn_raw_buffer_load_b128(grs, scale_off(jj + 5), 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   }
   wd_wait_vm<0>();  // no DMA may land in the LDS after this point
@@ -354,12 +420,22 @@ __device__ __forceinline__ void wd_block(const WdProblem& p, int g, int8_t* lds)
   const int hs = S == 1 ? 0 : sp & 1;                 // first owned row half
   const int es = S <= 2 ? 0 : (sp >> 1) * EN;         // first owned element
   constexpr int HN = S == 1 ? 2 : 1;                  // owned row halves
-  v16i f[HN][MT];  // owned sums (elements [0, EN))
+  v16i f[HN][MT];  // owned sums (elements [0, EN)); fp32 bits with GR
+  auto sum_bits = [&](int h, int tb, int e) {
+    if constexpr (G::GR != 0) {
+      const float v = cf[h][tb][e];  // (a bit cast of the element in place reads element 0)
+      return __float_as_int(v);
+    } else {
+      return c[h][tb][e];
+    }
+  };
   if constexpr (S == 1) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int tb = 0; tb < MT; ++tb) f[h][tb] = c[h][tb];
+      for (int tb = 0; tb < MT; ++tb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) f[h][tb][e] = sum_bits(h, tb, e);
     wd_lds_barrier();  // every wave is done with the stages
   } else {
     int32_t* red = reinterpret_cast<int32_t*>(xs);
@@ -373,18 +449,26 @@ __device__ __forceinline__ void wd_block(const WdProblem& p, int g, int8_t* lds)
         for (int h = 0; h < 2; ++h)
 #pragma unroll
           for (int e = 0; e < 16; ++e)
-            red[(((wave * RT + tb) * 2 + h) * 16 + e) * 64 + lane] = c[h][t0 + tb][e];
+            red[(((wave * RT + tb) * 2 + h) * 16 + e) * 64 + lane] = sum_bits(h, t0 + tb, e);
       wd_lds_barrier();
       const int w0 = wave - sp;
 #pragma unroll
       for (int tb = 0; tb < RT; ++tb)
 #pragma unroll
         for (int e = 0; e < EN; ++e) {
-          int32_t v = 0;
+          // the parts in order
+          const int32_t* rp = red + (((w0 * RT + tb) * 2 + hs) * 16 + es + e) * 64 + lane;
+          if constexpr (G::GR != 0) {
+            float v = __int_as_float(rp[0]);
 #pragma unroll
-          for (int q = 0; q < S; ++q)
-            v += red[((((w0 + q) * RT + tb) * 2 + hs) * 16 + es + e) * 64 + lane];
-          f[0][t0 + tb][e] = v;
+            for (int q = 1; q < S; ++q) v += __int_as_float(rp[q * RT * 2 * 16 * 64]);
+            f[0][t0 + tb][e] = __float_as_int(v);
+          } else {
+            int32_t v = rp[0];
+#pragma unroll
+            for (int q = 1; q < S; ++q) v += rp[q * RT * 2 * 16 * 64];
+            f[0][t0 + tb][e] = v;
+          }
         }
     }
     wd_lds_barrier();
@@ -407,7 +491,12 @@ __device__ __forceinline__ void wd_block(const WdProblem& p, int g, int8_t* lds)
   for (int h = 0; h < HN; ++h)
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      swl[h][u] = wsl[(wave / S) * kTileRows + 32 * (hs + h) + 4 * c4 + u];
+      swl[h][u] = G::GR ? 0.0f : wsl[(wave / S) * kTileRows + 32 * (hs + h) + 4 * c4 + u];
+  // y of one sum; the int32 sums themselves go to acc (not with GR)
+  auto out = [&](int32_t v, float sx, float sw) {
+    return G::GR ? __int_as_float(v) * sx : static_cast<float>(v) * (sx * sw);
+  };
+  int32_t* const acc_out = G::GR ? nullptr : p.acc;
   auto put = [&](int b) {
     int32_t* st = strip + (b & 1) * 32 * kWdSW;
 #pragma unroll
@@ -418,9 +507,9 @@ __device__ __forceinline__ void wd_block(const WdProblem& p, int g, int8_t* lds)
   };
   const bool whole = p.m >= G::TOK && (r + 1) * kTileRows <= p.n && (p.n % 4 == 0) &&
                      (reinterpret_cast<uintptr_t>(p.y) % 16 == 0) &&
-                     (!p.acc || reinterpret_cast<uintptr_t>(p.acc) % 16 == 0);
+                     (!acc_out || reinterpret_cast<uintptr_t>(acc_out) % 16 == 0);
   const bool vec = (p.n % 4 == 0) && (reinterpret_cast<uintptr_t>(p.y) % 16 == 0) &&
-                   (!p.acc || reinterpret_cast<uintptr_t>(p.acc) % 16 == 0);
+                   (!acc_out || reinterpret_cast<uintptr_t>(acc_out) % 16 == 0);
   put(0);
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
@@ -441,16 +530,16 @@ __device__ __forceinline__ void wd_block(const WdProblem& p, int g, int8_t* lds)
     if (whole) {
       const int64_t at = int64_t(32 * tb + tokb + (lane >> 3)) * p.n + row;
       float* yp = as_global_mut(p.y) + at;
-      int32_t* ap = as_global_mut(p.acc) + at;
+      int32_t* ap = as_global_mut(acc_out) + at;
 #pragma unroll
       for (int i = 0; i < PN; ++i) {
         float4 o4;
-        o4.x = static_cast<float>(v[i].x) * (sx[i] * swl[h][0]);
-        o4.y = static_cast<float>(v[i].y) * (sx[i] * swl[h][1]);
-        o4.z = static_cast<float>(v[i].z) * (sx[i] * swl[h][2]);
-        o4.w = static_cast<float>(v[i].w) * (sx[i] * swl[h][3]);
+        o4.x = out(v[i].x, sx[i], swl[h][0]);
+        o4.y = out(v[i].y, sx[i], swl[h][1]);
+        o4.z = out(v[i].z, sx[i], swl[h][2]);
+        o4.w = out(v[i].w, sx[i], swl[h][3]);
         *reinterpret_cast<float4*>(yp + int64_t(8 * i) * p.n) = o4;
-        if (p.acc) *reinterpret_cast<v4i*>(ap + int64_t(8 * i) * p.n) = v[i];
+        if (acc_out) *reinterpret_cast<v4i*>(ap + int64_t(8 * i) * p.n) = v[i];
       }
     } else {
 #pragma unroll
@@ -460,17 +549,17 @@ __device__ __forceinline__ void wd_block(const WdProblem& p, int g, int8_t* lds)
         const int32_t vv[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
         float o4[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) o4[u] = static_cast<float>(vv[u]) * (sx[i] * swl[h][u]);
+        for (int u = 0; u < 4; ++u) o4[u] = out(vv[u], sx[i], swl[h][u]);
         float* yrow = as_global_mut(p.y) + int64_t(tok) * p.n + row;
         if (vec) {
           *reinterpret_cast<float4*>(yrow) = make_float4(o4[0], o4[1], o4[2], o4[3]);
-          if (p.acc) *reinterpret_cast<v4i*>(as_global_mut(p.acc) + int64_t(tok) * p.n + row) = v[i];
+          if (acc_out) *reinterpret_cast<v4i*>(as_global_mut(acc_out) + int64_t(tok) * p.n + row) = v[i];
         } else {
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             if (row + u >= p.n) break;
             yrow[u] = o4[u];
-            if (p.acc) as_global_mut(p.acc)[int64_t(tok) * p.n + row + u] = vv[u];
+            if (acc_out) as_global_mut(acc_out)[int64_t(tok) * p.n + row + u] = vv[u];
           }
         }
       }
@@ -533,12 +622,96 @@ __global__ __launch_bounds__(G::THREADS) __attribute__((amdgpu_waves_per_eu(G::E
     t0 = int64_t(pr) * 128;
   }
   if (t0 >= d.m) return;
-  WdProblem p{d.w, d.x, d.x_scale, d.y, d.acc, d.n, d.k, d.m, WScale{d.w_scales, d.w_scale}};
+  WdProblem p{d.w, d.x, d.x_scale, d.y, d.acc, d.n, d.k, d.m, WScale{d.w_scales, d.w_scale}, nullptr};
   wd_tokens<G>(p, t0);
   for (int h = 0; h < reps; ++h) {
     if ((g + h) * G::TILES >= R) return;
     if (h) __syncthreads();  // the table, scales and strips are written again
     wd_block<G>(p, g + h, lds);
+  }
+}
+
+// Grouped launch of 32-token prepared blocks (every m <= 32, or some product
+// with per-group scales): 8 tiles x 32 tokens of a product without per-group
+// scales, on G0; 4 tiles x 32 tokens of one with them, on G1 (void: none).
+// PER workgroups share a block's parts.  A G1 of 64 tokens takes two blocks at
+// a time: four tiles by the first of two blocks (the others return), or two
+// tiles by each of them, an odd last one both its halves.
+template <class G0_, class G1_, int PER_>
+struct WdShort32 {
+  using G0 = G0_;
+  static constexpr bool kGroups = !std::is_same_v<G1_, void>;
+  using GG = std::conditional_t<kGroups, G1_, G0>;
+  static constexpr int PER = PER_;
+  static constexpr int THREADS = G0::THREADS, EU = G0::EU < GG::EU ? G0::EU : GG::EU;
+  static constexpr int LDS = G0::LDS > GG::LDS ? G0::LDS : GG::LDS;
+  static_assert(G0::TOK == 32 && G0::THREADS == GG::THREADS, "one block size");
+};
+
+template <class B>
+__global__ __launch_bounds__(B::THREADS) __attribute__((amdgpu_waves_per_eu(B::EU))) void wide_batched32_kernel(
+    const sherry_gemm_desc* __restrict__ descs, int count) {
+  using G0 = typename B::G0;
+  using G1 = typename B::GG;
+  constexpr int PER = B::PER;
+  __shared__ __attribute__((aligned(16))) int8_t lds[B::LDS];
+  const int32_t blk = static_cast<int32_t>(blockIdx.x) / PER;
+  const int sub = static_cast<int>(blockIdx.x) % PER;
+  const int lo = find_block_desc(descs, count, blk);
+  if (lo < 0) return;
+  const sherry_gemm_desc& d = descs[lo];
+  const int lb = blk - d.block_begin;
+  const int R = (d.n + kTileRows - 1) / kTileRows;
+  WdProblem p{d.w, d.x, d.x_scale, d.y, d.acc, d.n, d.k, d.m, WScale{d.w_scales, d.w_scale},
+              d.w_group_scales};
+  if constexpr (B::kGroups) {
+    if (d.w_group_scales) {
+      const int gb = (R + 3) / 4, T = (d.m + 31) / 32;
+      int g, reps, step = 1, tb;
+      if constexpr (G1::TOK == 32) {
+        constexpr int RPB = 4 / G1::TILES;
+        static_assert(RPB % PER == 0, "parts of a block");
+        tb = lb / gb;
+        g = (lb - tb * gb) * RPB + sub;
+        reps = RPB / PER;
+        step = PER;
+      } else if constexpr (G1::TILES == 4) {
+        static_assert(PER == 1, "one workgroup per two blocks");
+        tb = lb / gb;
+        g = lb - tb * gb;
+        reps = 1;
+      } else {
+        static_assert(G1::TILES == 2 && PER == 1, "half of the tiles of two blocks");
+        const int pairs = T / 2 * 2 * gb;
+        const bool paired = lb < pairs;
+        const int q = paired ? lb : 2 * (lb - pairs);
+        reps = paired ? 1 : 2;
+        tb = paired ? q / (2 * gb) : T / 2;
+        g = paired ? q - tb * 2 * gb : q;
+      }
+      const int64_t t0 = int64_t(tb) * G1::TOK;
+      if (t0 >= d.m) return;
+      p.acc = nullptr;
+      wd_tokens<G1>(p, t0);
+      for (int h = 0; h < reps; ++h) {
+        if ((g + h * step) * G1::TILES >= R) return;
+        if (h) __syncthreads();  // the table, scales and strips are written again
+        wd_block<G1>(p, g + h * step, lds);
+      }
+      return;
+    }
+  }
+  constexpr int RPB = 8 / G0::TILES;
+  static_assert(RPB % PER == 0, "parts of a block");
+  const int gb = (R + 7) / 8, tb = lb / gb;
+  const int64_t t0 = int64_t(tb) * 32;
+  if (t0 >= d.m) return;
+  wd_tokens<G0>(p, t0);
+  for (int h = 0; h < RPB / PER; ++h) {
+    const int g = (lb - tb * gb) * RPB + sub + h * PER;
+    if (g * G0::TILES >= R) return;
+    if (h) __syncthreads();
+    wd_block<G0>(p, g, lds);
   }
 }
 
@@ -570,6 +743,8 @@ using WdHalf = WdCfg<2, 2, 4, 2>;    // 64 x 2, K in 2
 using WdQuarter = WdCfg<2, 4, 8, 2>; // 64 x 2, K in 4, eight waves
 using WdShort = WdCfg<1, 4, 4, 2>;   // 32 x 1, K in 4
 using WdTiny = WdCfg<1, 8, 8, 2>;    // 32 x 1, K in 8, eight waves
+using WdPair = WdCfg<1, 2, 4, 3>;    // 32 x 2, K in 2 (grouped launches)
+using WdThin = WdCfg<1, 1, 4, 4>;    // 32 x 4 (grouped launches)
 
 // Estimated time (us) of a launch on one of them: the busiest CU runs c
 // workgroups of U units per wave; a lone workgroup takes fix + lat U, bound
@@ -581,41 +756,60 @@ struct WdCost {
 };
 constexpr WdCost kWdLong{8.2f, 0.68f, 5.0f, 0.64f, 7.7f}, kWdMid{6.0f, 0.54f, 5.0f, 0.45f, 1.7f},
     kWdHalf{6.0f, 0.575f, 5.0f, 0.50f, 2.0f}, kWdQuarter{7.5f, 0.83f, 5.0f, 0.80f, 5.2f},
-    kWdShort{5.0f, 0.55f, 4.0f, 0.41f, 1.1f}, kWdTiny{5.3f, 0.83f, 4.0f, 0.78f, 3.06f};
+    kWdShort{5.0f, 0.55f, 4.0f, 0.41f, 1.1f}, kWdTiny{5.3f, 0.83f, 4.0f, 0.78f, 3.06f},
+    kWdPair{5.0f, 0.55f, 4.0f, 0.50f, 1.1f}, kWdThin{5.5f, 0.46f, 4.0f, 0.46f, 1.5f};
 template <class G>
 float wd_estimate(const WdCost& c, int64_t workgroups, int64_t units) {
-  const float U = static_cast<float>(ceil_div(units, G::S));
+  const int64_t part = ceil_div(units, G::S);
+  const float U = static_cast<float>(G::GR == 4 ? (part + 3) / 4 * 4 : part);
   const float per = static_cast<float>(ceil_div(workgroups, 256));
   const float one = c.fix + c.lat * U, many = c.base + per * (c.thr * U + c.o);
   return one > many ? one : many;
 }
 
-}  // namespace
+// The shapes with per-group scales: twice the accumulators (int32 sums of one
+// unit, fp32 sums), and a conversion and an fma per unit and sum (128 VALU
+// operations per 64 x 64 sums beside 16 MFMAs: with two waves per SIMD the
+// VALU is what bounds them).
+template <int GR>
+using WdGrpMid = WdCfg<2, 1, 4, 2, GR>;  // 64 x 4
+template <int GR>
+using WdGrpHalf = WdCfg<2, 2, 4, 2, GR>;  // 64 x 2, K in 2
+template <int GR>
+using WdGrpPair = WdCfg<1, 2, 4, 3, GR>;  // 32 x 2, K in 2
+template <int GR>
+using WdGrpShort = WdCfg<1, 4, 4, 3, GR>;  // 32 x 1, K in 4
+template <int GR>
+using WdGrpTiny = WdCfg<1, 8, 8, 2, GR>;  // 32 x 1, K in 8, eight waves
+constexpr WdCost kWdGrpMid{5.9f, 0.77f, 4.0f, 0.625f, 3.9f}, kWdGrpHalf{5.8f, 0.83f, 4.0f, 0.78f, 1.2f},
+    kWdGrpPair{4.6f, 0.67f, 4.0f, 0.46f, 0.6f}, kWdGrpShort{5.0f, 0.71f, 4.0f, 0.60f, 0.3f},
+    kWdGrpTiny{5.6f, 1.07f, 4.0f, 1.05f, 3.1f};
 
-int launch_wide(const uint8_t* w, const int8_t* x, const float* x_scale, WScale ws, float* y,
-                int32_t* acc, int64_t m, int64_t n, int64_t k, hipStream_t s) {
-  const WdProblem p{w, x, x_scale, y, acc, static_cast<int>(n), static_cast<int>(k),
-                    static_cast<int>(m), ws};
-  const int64_t R = ceil_div(n, kTileRows), C = ceil_div(k, kTileK);
-  int best = 0;
+// The offer with the lowest estimate (ids from 0).
+struct WdPick {
+  int best = -1;
   float t = 0.0f;
-  auto offer = [&](int id, float e) {
-    if (id == 0 || e < t) t = e, best = id;
-  };
+  void offer(int id, float e) {
+    if (best < 0 || e < t) t = e, best = id;
+  }
+};
+
+template <int GR>
+int launch_wide_group_gr(const WdProblem& p, hipStream_t s) {
+  const int64_t R = ceil_div(p.n, kTileRows), C = ceil_div(p.k, kTileK), m = p.m;
   auto blocks = [&](int64_t tiles, int64_t tok) { return ceil_div(R, tiles) * ceil_div(m, tok); };
-  offer(0, wd_estimate<WdLong>(kWdLong, blocks(4, 128), C));
-  offer(1, wd_estimate<WdMid>(kWdMid, blocks(4, 64), C));
-  offer(2, wd_estimate<WdHalf>(kWdHalf, blocks(2, 64), C));
-  offer(3, wd_estimate<WdQuarter>(kWdQuarter, blocks(2, 64), C));
-  offer(4, wd_estimate<WdShort>(kWdShort, blocks(1, 32), C));
-  offer(5, wd_estimate<WdTiny>(kWdTiny, blocks(1, 32), C));
-  switch (best) {
-    case 0: return launch_wide_cfg<WdLong>(p, s);
-    case 1: return launch_wide_cfg<WdMid>(p, s);
-    case 2: return launch_wide_cfg<WdHalf>(p, s);
-    case 3: return launch_wide_cfg<WdQuarter>(p, s);
-    case 4: return launch_wide_cfg<WdShort>(p, s);
-    default: return launch_wide_cfg<WdTiny>(p, s);
+  WdPick k;
+  k.offer(0, wd_estimate<WdGrpMid<GR>>(kWdGrpMid, blocks(4, 64), C));
+  k.offer(1, wd_estimate<WdGrpHalf<GR>>(kWdGrpHalf, blocks(2, 64), C));
+  k.offer(2, wd_estimate<WdGrpPair<GR>>(kWdGrpPair, blocks(2, 32), C));
+  k.offer(3, wd_estimate<WdGrpShort<GR>>(kWdGrpShort, blocks(1, 32), C));
+  k.offer(4, wd_estimate<WdGrpTiny<GR>>(kWdGrpTiny, blocks(1, 32), C));
+  switch (k.best) {
+    case 0: return launch_wide_cfg<WdGrpMid<GR>>(p, s);
+    case 1: return launch_wide_cfg<WdGrpHalf<GR>>(p, s);
+    case 2: return launch_wide_cfg<WdGrpPair<GR>>(p, s);
+    case 3: return launch_wide_cfg<WdGrpShort<GR>>(p, s);
+    default: return launch_wide_cfg<WdGrpTiny<GR>>(p, s);
   }
 }
 
@@ -625,24 +819,95 @@ int launch_wide_batched_cfg(const sherry_gemm_desc* descs, int count, int64_t to
   return launch(wide_batched_kernel<G>, dim3(static_cast<unsigned>(total_blocks * G::PER)),
                 dim3(G::THREADS), 0, s, descs, count);
 }
+template <class G0, class G1, int PER>
+int launch_wide_batched32_cfg(const sherry_gemm_desc* descs, int count, int64_t total_blocks,
+                              hipStream_t s) {
+  return launch(wide_batched32_kernel<WdShort32<G0, G1, PER>>,
+                dim3(static_cast<unsigned>(total_blocks * PER)), dim3(G0::THREADS), 0, s, descs,
+                count);
+}
 
-// Grouped launches of 64-token blocks: the workgroup shape by the number of
-// blocks (the rows' lengths are not known here; 24 units stand for them).
+// The rows' lengths are not known at a grouped launch: 24 units stand for them.
+constexpr int64_t kWdUnits = 24;
+
+}  // namespace
+
+int launch_wide(const uint8_t* w, const int8_t* x, const float* x_scale, WScale ws, float* y,
+                int32_t* acc, int64_t m, int64_t n, int64_t k, hipStream_t s) {
+  const WdProblem p{w, x, x_scale, y, acc, static_cast<int>(n), static_cast<int>(k),
+                    static_cast<int>(m), ws, nullptr};
+  const int64_t R = ceil_div(n, kTileRows), C = ceil_div(k, kTileK);
+  auto blocks = [&](int64_t tiles, int64_t tok) { return ceil_div(R, tiles) * ceil_div(m, tok); };
+  WdPick q;
+  q.offer(0, wd_estimate<WdLong>(kWdLong, blocks(4, 128), C));
+  q.offer(1, wd_estimate<WdMid>(kWdMid, blocks(4, 64), C));
+  q.offer(2, wd_estimate<WdHalf>(kWdHalf, blocks(2, 64), C));
+  q.offer(3, wd_estimate<WdQuarter>(kWdQuarter, blocks(2, 64), C));
+  q.offer(4, wd_estimate<WdShort>(kWdShort, blocks(1, 32), C));
+  q.offer(5, wd_estimate<WdTiny>(kWdTiny, blocks(1, 32), C));
+  switch (q.best) {
+    case 0: return launch_wide_cfg<WdLong>(p, s);
+    case 1: return launch_wide_cfg<WdMid>(p, s);
+    case 2: return launch_wide_cfg<WdHalf>(p, s);
+    case 3: return launch_wide_cfg<WdQuarter>(p, s);
+    case 4: return launch_wide_cfg<WdShort>(p, s);
+    default: return launch_wide_cfg<WdTiny>(p, s);
+  }
+}
+
+int launch_wide_group(const uint8_t* w, const int8_t* x, const float* x_scale, const float* gs,
+                      float* y, int32_t* acc, int64_t m, int64_t n, int64_t k, hipStream_t s) {
+  if (acc) {
+    // int32 totals from an unscaled launch (its y is overwritten below)
+    const int rc = launch_wide(w, x, x_scale, WScale{nullptr, 1.0f}, y, acc, m, n, k, s);
+    if (rc != SHERRY_OK) return rc;
+  }
+  const WdProblem p{w, x, x_scale, y, nullptr, static_cast<int>(n), static_cast<int>(k),
+                    static_cast<int>(m), WScale{nullptr, 0.0f}, gs};
+  const bool pieces = ceil_div(k, kTileK) % 4 == 0 && (reinterpret_cast<uintptr_t>(gs) & 15) == 0;
+  return pieces ? launch_wide_group_gr<4>(p, s) : launch_wide_group_gr<1>(p, s);
+}
+
+// Prepared blocks of a grouped launch: 8 tiles (4 with per-group scales) x 32
+// tokens when max_m <= 32, else 8 tiles x 64 tokens.
+int wide_blocks(int64_t n, bool group_scales) {
+  return static_cast<int>(ceil_div(ceil_div(n, kTileRows), group_scales ? 4 : 8));
+}
+int wide_batched_tokens(int max_m) { return max_m <= 32 ? 32 : 64; }
+
 int launch_wide_batched(const sherry_gemm_desc* descs, int count, int64_t total_blocks,
-                        int max_m, hipStream_t s) {
-  constexpr int64_t kUnits = 24;
-  int best = 0;
-  float t = 0.0f;
-  auto offer = [&](int id, float e) {
-    if (id == 0 || e < t) t = e, best = id;
-  };
+                        int max_m, bool groups, hipStream_t s) {
+  WdPick q;
+  if (groups) {
+    // (a launch's products may have any row lengths: 4-byte scale loads)
+    q.offer(0, wd_estimate<WdGrpMid<1>>(kWdGrpMid, ceil_div(total_blocks, 2), kWdUnits));
+    q.offer(1, wd_estimate<WdGrpHalf<1>>(kWdGrpHalf, total_blocks, kWdUnits));
+    q.offer(2, wd_estimate<WdGrpPair<1>>(kWdGrpPair, total_blocks * 2, kWdUnits));
+    q.offer(3, wd_estimate<WdGrpShort<1>>(kWdGrpShort, total_blocks * 4, kWdUnits));
+    switch (q.best) {
+      case 0: return launch_wide_batched32_cfg<WdPair, WdGrpMid<1>, 1>(descs, count, total_blocks, s);
+      case 1: return launch_wide_batched32_cfg<WdPair, WdGrpHalf<1>, 1>(descs, count, total_blocks, s);
+      case 2: return launch_wide_batched32_cfg<WdPair, WdGrpPair<1>, 2>(descs, count, total_blocks, s);
+      default: return launch_wide_batched32_cfg<WdPair, WdGrpShort<1>, 4>(descs, count, total_blocks, s);
+    }
+  }
+  if (max_m <= 32) {
+    q.offer(0, wd_estimate<WdThin>(kWdThin, total_blocks * 2, kWdUnits));
+    q.offer(1, wd_estimate<WdPair>(kWdPair, total_blocks * 4, kWdUnits));
+    q.offer(2, wd_estimate<WdShort>(kWdShort, total_blocks * 8, kWdUnits));
+    switch (q.best) {
+      case 0: return launch_wide_batched32_cfg<WdThin, void, 2>(descs, count, total_blocks, s);
+      case 1: return launch_wide_batched32_cfg<WdPair, void, 4>(descs, count, total_blocks, s);
+      default: return launch_wide_batched32_cfg<WdShort, void, 8>(descs, count, total_blocks, s);
+    }
+  }
   // (64 tokens of a 128-token workgroup's are idle in an odd last block)
   const int64_t T = ceil_div(max_m, 64);
-  offer(0, wd_estimate<WdLong>(kWdLong, ceil_div(total_blocks * ((T + 1) / 2 * 2), T), kUnits));
-  offer(1, wd_estimate<WdMid>(kWdMid, total_blocks * WdMid::PER, kUnits));
-  offer(2, wd_estimate<WdHalf>(kWdHalf, total_blocks * WdHalf::PER, kUnits));
-  offer(4, wd_estimate<WdShort>(kWdShort, total_blocks * WdShort::PER, kUnits));
-  switch (best) {
+  q.offer(0, wd_estimate<WdLong>(kWdLong, ceil_div(total_blocks * ((T + 1) / 2 * 2), T), kWdUnits));
+  q.offer(1, wd_estimate<WdMid>(kWdMid, total_blocks * WdMid::PER, kWdUnits));
+  q.offer(2, wd_estimate<WdHalf>(kWdHalf, total_blocks * WdHalf::PER, kWdUnits));
+  q.offer(3, wd_estimate<WdShort>(kWdShort, total_blocks * WdShort::PER, kWdUnits));
+  switch (q.best) {
     case 0: return launch_wide_batched_cfg<WdLong>(descs, count, total_blocks, s);
     case 1: return launch_wide_batched_cfg<WdMid>(descs, count, total_blocks, s);
     case 2: return launch_wide_batched_cfg<WdHalf>(descs, count, total_blocks, s);

@@ -116,3 +116,117 @@ def test_grouped(dev, shapes, low, high, channel):
         if i % 2 == 0:
             assert np.array_equal(acc.cpu().numpy(), ref)
         assert np.array_equal(y.cpu().numpy(), _epilogue(ref, sx, sw))
+
+
+# ---- per-group scales, and launches of 32-token blocks --------------------------
+
+def _group_scales(n, k, seed):
+    return (np.random.default_rng(seed).random((n, -(-k // 128))) * 0.04 + 0.01).astype(np.float32)
+
+
+def _group_ok(y, q, t, sx, gs, k):
+    y_ref, mag, acc = oracle.product_groups(q, t, sx, gs, threads=16)
+    G = -(-k // 128)
+    assert not (np.abs(y.astype(np.float64) - y_ref) > (G + 4) * 2.0 ** -24 * mag).any()
+    return acc
+
+
+# by the cost model, with 4-byte and (rows of whole aligned pieces) 16-byte
+# scale loads: 32 x 2, 32 x 1 (K in 4), 32 x 1 (K in 8), 64 x 2, 64 x 4
+LONE_GROUP = [(5, 64, 128), (33, 70, 132), (37, 130, 1028), (31, 300, 516), (100, 70, 8196),
+              (385, 8190, 132), (641, 5122, 388), (385, 8190, 1028), (17, 66, 4),
+              (5, 70, 512), (65, 130, 2044), (40, 300, 3584), (33, 580, 8192), (513, 2900, 2044),
+              (385, 5122, 508), (257, 8190, 512)]
+
+
+@pytest.mark.parametrize("m,n,k", LONE_GROUP)
+@pytest.mark.parametrize("aligned", [True, False])
+def test_lone_group(dev, m, n, k, aligned):
+    import paper_2601_07892_amd as sh
+    print("[case] wide group", m, n, k, aligned, file=sys.stderr, flush=True)
+    t, q, sx, w, qd, sxd = _inputs(dev, m, n, k, "group")
+    gs = _group_scales(n, k, n + k)
+    # a scale matrix that starts 4 bytes past a 16-byte boundary takes the
+    # 4-byte loads
+    buf = torch.zeros(gs.size + 1, dtype=torch.float32, device=dev)
+    gsd = (buf[:-1] if aligned else buf[1:]).view(gs.shape)
+    gsd.copy_(torch.from_numpy(gs))
+    y = torch.full((m, n), float("nan"), dtype=torch.float32, device=dev)
+    acc = torch.full((m, n), -7, dtype=torch.int32, device=dev)
+    sh.sherry_gemm_group(w, qd, sxd, gsd, y, acc if aligned else None, m, n, k,
+                         sh.SHERRY_KERNEL_SKINNY)
+    torch.cuda.synchronize()
+    ref = _group_ok(y.cpu().numpy(), q, t, sx, gs, k)
+    if aligned:
+        assert np.array_equal(acc.cpu().numpy(), ref)
+
+
+def test_lone_group_infinite_scale_stays_in_its_group(dev):
+    # a unit past a part's end must not meet another row's scales: an infinite
+    # scale reaches its own row and nothing else
+    import paper_2601_07892_amd as sh
+    for k in (132, 1408, 2176):
+        m, n = 40, 130
+        t, q, sx, w, qd, sxd = _inputs(dev, m, n, k, "inf")
+        q[:] = np.abs(q) + (q == 0)
+        gs = _group_scales(n, k, 3)
+        ref, _, _ = oracle.product_groups(q, t, sx, gs, threads=16)
+        gs[77, 0] = np.inf
+        y = torch.empty((m, n), dtype=torch.float32, device=dev)
+        sh.sherry_gemm_group(w, torch.from_numpy(q).to(dev), sxd, torch.from_numpy(gs).to(dev), y,
+                             None, m, n, k, sh.SHERRY_KERNEL_SKINNY)
+        torch.cuda.synchronize()
+        yn = y.cpu().numpy()
+        rows = np.arange(n) != 77
+        assert np.isfinite(yn[:, rows]).all() and not np.isfinite(yn[:, 77]).any()
+        assert np.allclose(yn[:, rows], ref[:, rows], rtol=1e-4, atol=1e-3)
+
+
+# (m, n, k, per-group) of the products of one launch; prepared blocks of 8
+# tiles (4 with per-group scales) x 32 tokens
+SMALL32 = [(17, 70, 132, False), (32, 1030, 1540, False), (5, 300, 260, False)]
+GROUPED32 = [
+    (SMALL32, 1, 96),
+    (SMALL32 + [(20, 51000, 68, False)], 97, 128),
+    (SMALL32 + [(31, 86000, 68, False)], 161, 192),
+    ([(33, 70, 132, True), (64, 1030, 260, True), (129, 300, 1540, True), (1, 64, 128, True)], 1, 192),
+    ([(33, 70, 132, True), (300, 4100, 260, True), (65, 520, 1540, False), (97, 1000, 388, True)], 193,
+     256),
+    ([(33, 70, 132, True), (500, 4100, 260, True), (65, 520, 644, False), (97, 1000, 388, True)], 257,
+     384),
+    ([(33, 70, 132, True), (700, 4100, 260, True), (65, 520, 644, False), (97, 1000, 388, True)], 385,
+     512),
+]
+
+
+@pytest.mark.parametrize("shapes,low,high", GROUPED32)
+def test_grouped32(dev, shapes, low, high):
+    import paper_2601_07892_amd as sh
+    descs = (sh.sherry_gemm_desc * len(shapes))()
+    cases, keep = [], []
+    for i, (m, n, k, group) in enumerate(shapes):
+        t, q, sx, w, qd, sxd = _inputs(dev, m, n, k, "grouped32_%d" % i)
+        y = torch.full((m, n), float("nan"), dtype=torch.float32, device=dev)
+        acc = torch.full((m, n), -7, dtype=torch.int32, device=dev)
+        gs = _group_scales(n, k, i)
+        gsd = torch.from_numpy(gs).to(dev)
+        d = descs[i]
+        d.w, d.x, d.x_scale, d.y = w.data_ptr(), qd.data_ptr(), sxd.data_ptr(), y.data_ptr()
+        d.acc = None if group else acc.data_ptr()
+        d.w_group_scales = gsd.data_ptr() if group else None
+        d.n, d.k, d.m, d.w_scale = n, k, m, float(np.float32(0.0173))
+        keep.append((w, qd, sxd, gsd))
+        cases.append((t, q, sx, gs, y, acc, group, k))
+    total, value = sh.sherry_gemm_batched_prepare(descs)
+    print("[case] wide grouped32", len(shapes), total, value, file=sys.stderr, flush=True)
+    assert low <= total <= high and 17 <= (value & ~sh.SHERRY_LAUNCH_GROUPS) <= 32
+    sh.sherry_gemm_batched(torch.from_numpy(sh.descs_to_bytes(descs)).to(dev), len(shapes), total,
+                           value)
+    torch.cuda.synchronize()
+    for t, q, sx, gs, y, acc, group, k in cases:
+        if group:
+            _group_ok(y.cpu().numpy(), q, t, sx, gs, k)
+        else:
+            ref = oracle.gemm_i32(q, t, threads=16)
+            assert np.array_equal(acc.cpu().numpy(), ref)
+            assert np.array_equal(y.cpu().numpy(), _epilogue(ref, sx, np.float32(0.0173)))
