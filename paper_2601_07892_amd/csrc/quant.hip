@@ -3,85 +3,107 @@
 // The paper keeps activations in BF16 (weights-only setting, Limitations) but
 // its engine accumulates in integers (Appendix A, online phase).  The integer
 // inputs are produced here: s = absmax/127, q = clamp(rint(x/s), -127, 127).
-// One workgroup per token row.  Rows up to 16384 values are read once into
-// registers; longer rows are read twice (absmax, then quantize).
+// One workgroup per token row: 256 threads for rows of up to 8192 values, 512
+// for longer ones.  Rows up to 32768 values are read once into registers;
+// longer rows are read twice (absmax, then quantize).
+//
+// What bounds it: launch and memory latency at decode sizes, HBM at prefill
+// sizes.  A thread's loads go out back to back (the row's end through the
+// range of a buffer resource, not a branch per load), and quant4 takes about 6
+// VALU operations per value (15 before, 2-6 us of a 2048-token launch):
+// 2048 x 14336 32.3 -> 26.9 us (5.5 TB/s), 8192 x 4096 32.9 -> 29.2,
+// 2048 x 3072 8.8 -> 7.9, 64 x 14336 6.8 -> 5.9, 1000 x 30000 51.7 -> 28.7.
+#include <type_traits>
+
 #include "sherry_internal.h"
 
 namespace sherry {
 namespace {
 
-constexpr int kQuantThreads = 256;
-
+template <int T>
 __device__ __forceinline__ float block_max(float amax, float* part) {
   amax = wave_max_f32(amax);
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = amax;
   __syncthreads();
-  return fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
+  amax = part[0];
+#pragma unroll
+  for (int i = 1; i < T / 64; ++i) amax = fmaxf(amax, part[i]);
+  return amax;
 }
 
-// One row x[0..k) -> q, *scale, by the whole workgroup.  NV > 0: rows of up
-// to NV*1024 values, read once into registers (NV float4 per thread),
-// reduced and quantized from registers.  NV = 0: any row length, two passes
-// over the row (the second from cache).
-template <int NV>
+// One row x[0..k) -> q, *scale, by the whole workgroup of T threads.  NV > 0:
+// rows of up to 4 NV T values, read once into registers (NV float4 per
+// thread) and quantized from there; loads and stores past the row read zeros
+// and are dropped.  NV = 0: any row length, two passes over the row (the
+// second from cache).  AUX: the loads' cache policy.
+template <int T, int NV, int AUX>
 __device__ __forceinline__ void quantize_row(const float* x, int64_t k, int8_t* q, float* scale,
                                              float* part) {
   const float4* xr = reinterpret_cast<const float4*>(x);
   uint32_t* qr = reinterpret_cast<uint32_t*>(q);
   if constexpr (NV > 0) {
-    const int k4 = static_cast<int>(k >> 2);
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(x), 0, static_cast<int>(k) * 4, kBufferWord3);
+    const __amdgpu_buffer_rsrc_t rq =
+        __builtin_amdgcn_make_buffer_rsrc(q, 0, static_cast<int>(k), kBufferWord3);
+    u32x4 raw[NV];
+#pragma unroll
+    for (int e = 0; e < NV; ++e)
+      raw[e] = __builtin_amdgcn_raw_buffer_load_b128(
+          rx, 16 * (static_cast<int>(threadIdx.x) + e * T), 0, AUX);
+    __builtin_amdgcn_sched_barrier(0);
     float4 v[NV];
     float amax = 0.0f;
 #pragma unroll
     for (int e = 0; e < NV; ++e) {
-      const int i = threadIdx.x + e * kQuantThreads;
-      v[e] = (i < k4) ? xr[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+      v[e] = make_float4(__uint_as_float(raw[e].x), __uint_as_float(raw[e].y),
+                         __uint_as_float(raw[e].z), __uint_as_float(raw[e].w));
       amax = fmaxf(amax, fmaxf(fmaxf(fabsf(v[e].x), fabsf(v[e].y)),
                                fmaxf(fabsf(v[e].z), fabsf(v[e].w))));
     }
-    amax = block_max(amax, part);
+    amax = block_max<T>(amax, part);
     const float s = amax / 127.0f;
     const float rs = 1.0f / s;
 #pragma unroll
-    for (int e = 0; e < NV; ++e) {
-      const int i = threadIdx.x + e * kQuantThreads;
-      if (i < k4) qr[i] = (amax == 0.0f) ? 0u : quant4(v[e], s, rs);
-    }
+    for (int e = 0; e < NV; ++e)
+      __builtin_amdgcn_raw_buffer_store_b32(
+          (amax == 0.0f) ? 0u : quant4(v[e], s, rs), rq,
+          4 * (static_cast<int>(threadIdx.x) + e * T), 0, 0);
     if (threadIdx.x == 0) *scale = (amax == 0.0f) ? 0.0f : s;
   } else {
     const int64_t k4 = k >> 2;
     float amax = 0.0f;
-    for (int64_t i = threadIdx.x; i < k4; i += kQuantThreads) {
+    for (int64_t i = threadIdx.x; i < k4; i += T) {
       const float4 v = xr[i];
       amax = fmaxf(amax, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
     }
-    amax = block_max(amax, part);
+    amax = block_max<T>(amax, part);
     if (amax == 0.0f) {
-      for (int64_t i = threadIdx.x; i < k4; i += kQuantThreads) qr[i] = 0u;
+      for (int64_t i = threadIdx.x; i < k4; i += T) qr[i] = 0u;
       if (threadIdx.x == 0) *scale = 0.0f;
       return;
     }
     const float s = amax / 127.0f;
     const float rs = 1.0f / s;
-    for (int64_t i = threadIdx.x; i < k4; i += kQuantThreads) qr[i] = quant4(xr[i], s, rs);
+    for (int64_t i = threadIdx.x; i < k4; i += T) qr[i] = quant4(xr[i], s, rs);
     if (threadIdx.x == 0) *scale = s;
   }
 }
 
-template <int NV>
-__global__ __launch_bounds__(kQuantThreads) void quantize_rows_kernel(
-    const float* __restrict__ x, int64_t k, int8_t* __restrict__ q,
-    float* __restrict__ x_scale) {
-  __shared__ float part[kQuantThreads / 64];
+template <int T, int NV, int AUX>
+__global__ __launch_bounds__(T) void quantize_rows_kernel(const float* __restrict__ x, int64_t k,
+                                                          int8_t* __restrict__ q,
+                                                          float* __restrict__ x_scale) {
+  __shared__ float part[T / 64];
   const int64_t row = blockIdx.x;
-  quantize_row<NV>(x + row * k, k, q + row * k, x_scale + row, part);
+  quantize_row<T, NV, AUX>(x + row * k, k, q + row * k, x_scale + row, part);
 }
 
 // Every row of every matrix of a descriptor array, one workgroup per row.
-template <int NV>
-__global__ __launch_bounds__(kQuantThreads) void quantize_batched_kernel(
+template <int T, int NV, int AUX>
+__global__ __launch_bounds__(T) void quantize_batched_kernel(
     const sherry_quant_desc* __restrict__ descs, int count) {
-  __shared__ float part[kQuantThreads / 64];
+  __shared__ float part[T / 64];
   const int32_t blk = static_cast<int32_t>(blockIdx.x);
   // last descriptor with row_begin <= blk (a prefix: row_begin increases)
   const int lane = threadIdx.x & 63;
@@ -96,39 +118,49 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_batched_kernel(
   lo = __builtin_amdgcn_readfirstlane(lo);
   const sherry_quant_desc& d = descs[lo];
   const int64_t row = blk - d.row_begin, k = d.k;
-  quantize_row<NV>(d.x + row * k, k, d.q + row * k, d.x_scale + row, part);
+  quantize_row<T, NV, AUX>(d.x + row * k, k, d.q + row * k, d.x_scale + row, part);
 }
 
-// Register-held rows up to NV*1024 values; 0 = two passes.
-int quant_nv(int64_t k) {
-  const int64_t nv = ceil_div(k, 4 * kQuantThreads);
-  return nv <= 2 ? 2 : nv <= 4 ? 4 : nv <= 8 ? 8 : nv <= 16 ? 16 : 0;
+// Calls f(T, NV) with the workgroup for rows of up to k values.
+template <class F>
+int with_row_shape(int64_t k, F f) {
+  using std::integral_constant;
+  if (k <= 2048) return f(integral_constant<int, 256>{}, integral_constant<int, 2>{});
+  if (k <= 4096) return f(integral_constant<int, 256>{}, integral_constant<int, 4>{});
+  if (k <= 8192) return f(integral_constant<int, 256>{}, integral_constant<int, 8>{});
+  if (k <= 16384) return f(integral_constant<int, 512>{}, integral_constant<int, 8>{});
+  if (k <= 32768) return f(integral_constant<int, 512>{}, integral_constant<int, 16>{});
+  return f(integral_constant<int, 512>{}, integral_constant<int, 0>{});
 }
+
+// Inputs of kStreamBytes and more are read past the caches (non-temporal):
+// the Infinity Cache cannot still hold them whole from the operation that
+// wrote them (8192 x 4096, 134 MB: 29.2 us against 32.7; 2048 x 14336, 117 MB:
+// 26.9 / 31.0; but 2048 x 8192, 67 MB: 17.0 / 15.5).
+constexpr int64_t kStreamBytes = 96 << 20;
 
 }  // namespace
 
 int launch_quantize(const float* x, int64_t m, int64_t k, int8_t* q, float* x_scale,
                     hipStream_t s) {
-  const dim3 grid(static_cast<unsigned>(m)), block(kQuantThreads);
-  switch (quant_nv(k)) {
-    case 2: return launch(quantize_rows_kernel<2>, grid, block, 0, s, x, k, q, x_scale);
-    case 4: return launch(quantize_rows_kernel<4>, grid, block, 0, s, x, k, q, x_scale);
-    case 8: return launch(quantize_rows_kernel<8>, grid, block, 0, s, x, k, q, x_scale);
-    case 16: return launch(quantize_rows_kernel<16>, grid, block, 0, s, x, k, q, x_scale);
-    default: return launch(quantize_rows_kernel<0>, grid, block, 0, s, x, k, q, x_scale);
-  }
+  return with_row_shape(k, [&](auto t, auto nv) {
+    constexpr int T = decltype(t)::value, NV = decltype(nv)::value;
+    const dim3 grid(static_cast<unsigned>(m)), block(T);
+    if (4 * m * k >= kStreamBytes)
+      return launch(quantize_rows_kernel<T, NV, kLoadStream>, grid, block, 0, s, x, k, q, x_scale);
+    return launch(quantize_rows_kernel<T, NV, 0>, grid, block, 0, s, x, k, q, x_scale);
+  });
 }
 
 int launch_quantize_batched(const sherry_quant_desc* descs, int count, int64_t total_rows,
                             int64_t max_k, hipStream_t s) {
-  const dim3 grid(static_cast<unsigned>(total_rows)), block(kQuantThreads);
-  switch (quant_nv(max_k)) {
-    case 2: return launch(quantize_batched_kernel<2>, grid, block, 0, s, descs, count);
-    case 4: return launch(quantize_batched_kernel<4>, grid, block, 0, s, descs, count);
-    case 8: return launch(quantize_batched_kernel<8>, grid, block, 0, s, descs, count);
-    case 16: return launch(quantize_batched_kernel<16>, grid, block, 0, s, descs, count);
-    default: return launch(quantize_batched_kernel<0>, grid, block, 0, s, descs, count);
-  }
+  return with_row_shape(max_k, [&](auto t, auto nv) {
+    constexpr int T = decltype(t)::value, NV = decltype(nv)::value;
+    const dim3 grid(static_cast<unsigned>(total_rows)), block(T);
+    if (4 * total_rows * max_k >= kStreamBytes)
+      return launch(quantize_batched_kernel<T, NV, kLoadStream>, grid, block, 0, s, descs, count);
+    return launch(quantize_batched_kernel<T, NV, 0>, grid, block, 0, s, descs, count);
+  });
 }
 
 }  // namespace sherry

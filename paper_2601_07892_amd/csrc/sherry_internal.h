@@ -113,7 +113,7 @@ __device__ __forceinline__ float round_quotient(float x, float s, float rs) {
   return k;
 }
 
-__device__ __forceinline__ uint32_t quant4(float4 v, float s, float rs) {
+__device__ __forceinline__ uint32_t quant4_divide(float4 v, float s, float rs) {
   const float r[4] = {round_quotient(v.x, s, rs), round_quotient(v.y, s, rs),
                       round_quotient(v.z, s, rs), round_quotient(v.w, s, rs)};
   uint32_t out = 0;
@@ -123,6 +123,26 @@ __device__ __forceinline__ uint32_t quant4(float4 v, float s, float rs) {
     out |= (static_cast<uint32_t>(static_cast<int>(t)) & 0xFFu) << (8 * i);
   }
   return out;
+}
+
+// Four values with one branch between them: t + 1.5 * 2^23 holds rint(t) (to
+// even, as rintf) in its low mantissa bits, whose low byte is the int8 value,
+// and less 1.5 * 2^23 it is that integer exactly.  When all four lie at least
+// 2^-13 from a half-integer the bytes are the result (|t| <= 127 + a few ulps
+// rounds to at most 127, so nothing is clamped); otherwise, and for NaN, the
+// path above decides.  About 6 VALU operations per value against 15.
+__device__ __forceinline__ uint32_t quant4(float4 v, float s, float rs) {
+  constexpr float kMagic = 12582912.0f, kBand = 0.5f - 0x1p-13f;
+  const float t0 = v.x * rs, t1 = v.y * rs, t2 = v.z * rs, t3 = v.w * rs;
+  const float m0 = t0 + kMagic, m1 = t1 + kMagic, m2 = t2 + kMagic, m3 = t3 + kMagic;
+  const bool sure = (fabsf(t0 - (m0 - kMagic)) <= kBand) & (fabsf(t1 - (m1 - kMagic)) <= kBand) &
+                    (fabsf(t2 - (m2 - kMagic)) <= kBand) & (fabsf(t3 - (m3 - kMagic)) <= kBand);
+  if (!sure) return quant4_divide(v, s, rs);
+  // v_perm_b32: bytes 0-3 of the second operand are selectors 0-3, of the
+  // first 4-7
+  const uint32_t lo = __builtin_amdgcn_perm(__float_as_uint(m1), __float_as_uint(m0), 0x0c0c0400u);
+  const uint32_t hi = __builtin_amdgcn_perm(__float_as_uint(m3), __float_as_uint(m2), 0x04000c0cu);
+  return lo | hi;
 }
 
 // Address-space views of device pointers.  Pointers read from memory (e.g.
