@@ -133,11 +133,13 @@ int with_row_shape(int64_t k, F f) {
   return f(integral_constant<int, 512>{}, integral_constant<int, 0>{});
 }
 
-// Inputs of kStreamBytes and more are read past the caches (non-temporal):
-// the Infinity Cache cannot still hold them whole from the operation that
-// wrote them (8192 x 4096, 134 MB: 29.2 us against 32.7; 2048 x 14336, 117 MB:
-// 26.9 / 31.0; but 2048 x 8192, 67 MB: 17.0 / 15.5).
-constexpr int64_t kStreamBytes = 96 << 20;
+// Inputs of kStreamBytes and more are read past the caches (non-temporal), as
+// they are read once: 8192 x 4096 (134 MB) 32.7 -> 29.2 us, 2048 x 14336 31.0
+// -> 26.9, 512 x 8192 (17 MB) 7.5 -> 6.8, and a LLaMA-3.2-3B layer at 2048
+// tokens, whose inputs follow outputs as large through the caches, 264 -> 257.
+// (A loop over inputs that stay in the Infinity Cache is slower: 2048 x 8192
+// 15.5 -> 17.0.)  Smaller ones are left in the caches.
+constexpr int64_t kStreamBytes = 8 << 20;
 
 }  // namespace
 
