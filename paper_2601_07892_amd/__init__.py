@@ -180,6 +180,17 @@ def _load():
 lib = _load()
 
 
+def _torch_handles():
+    import torch
+    return (getattr(torch._C, "_cuda_getCurrentRawStream", None),
+            getattr(torch._C, "_cuda_getDevice", None))
+
+
+_raw_stream, _current_device = _torch_handles()
+if _current_device is None:
+    _raw_stream = None
+
+
 def _status_str(st: int) -> str:
     return lib.sherry_status_str(int(st)).decode()
 
@@ -201,9 +212,18 @@ def _ptr(t) -> int | None:
 
 
 def _stream(stream) -> int | None:
+    """hipStream_t of a call: the given one, else torch's current stream.
+
+    torch.cuda.current_stream() builds a Stream object on every call (2.8 us,
+    more than the rest of a call's Python side together); the raw handle of the
+    same stream takes 0.2 us.  Used once torch has initialised the device and
+    where this torch has it.
+    """
     if stream is not None:
         return stream
     import torch
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(_current_device())
     return torch.cuda.current_stream().cuda_stream
 
 
