@@ -36,10 +36,13 @@ namespace {
 
 constexpr int kGemvThreads = 64 * kGemvWaves;
 constexpr int kRing = 3;  // containers per wave held in the register ring
-// The lane-interleaved decode keeps one container in flight beside the one
-// it decodes: measured 1-2% faster than three on the LLaMA-3.2-1B step (less
-// of the stream queued ahead of the workgroups that start late).
-constexpr int kIlRing = 2;
+// The one-token decode on the matrix cores and the decode of lane-interleaved
+// units keep one container in flight beside the one they decode: less of the
+// stream queued ahead of the workgroups that start late (1-2% faster than
+// three on the LLaMA-3.2-1B step), and with it 64 registers per lane, four
+// workgroups per CU (8B-scale one-token step on tiled units 200.7 us, with
+// three 206.2).
+constexpr int kShortRing = 2;
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
@@ -166,6 +169,28 @@ __device__ __forceinline__ void dot_container_mfma(const uint32_t (&d)[5], const
   }
 }
 
+// Codes [g, g + 16) of a container: chunk j of them into acc[j] (see
+// XFromLdsMfma).
+template <int g>
+__device__ __forceinline__ void dot_container_rows(const uint32_t (&d)[5], const u32x4& xw,
+                                                   const uint32_t* lut, v4i (&acc)[4]) {
+  __builtin_amdgcn_sched_barrier(0);
+  uint32_t a4[16];
+  group_offsets<g>(d, a4, std::make_integer_sequence<int, 16>{});
+  uint32_t wv[16];
+#pragma unroll
+  for (int j = 0; j < 16; ++j)
+    wv[j] = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(lut) + a4[j]);
+  const v4i a = {static_cast<int>(xw.x), static_cast<int>(xw.y), static_cast<int>(xw.z),
+                 static_cast<int>(xw.w)};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const v4i b = {static_cast<int>(wv[4 * j]), static_cast<int>(wv[4 * j + 1]),
+                   static_cast<int>(wv[4 * j + 2]), static_cast<int>(wv[4 * j + 3])};
+    acc[j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, acc[j], 0, 0, 0);
+  }
+}
+
 // Activation source: the activation words of container c, read with scalar
 // loads (wave-uniform) into SGPRs; dot masks the words past K of a partial
 // last container.
@@ -196,17 +221,26 @@ struct XFromLds {
   }
 };
 
-// The same activations as the A operand of dot_container_mfma: lanes 16b + b
-// read container c's words from xq (exec-masked LDS reads of 4 lanes); the
-// other lanes' registers keep the zeros they start with.
+// One token on the matrix cores.  The same activations as A operands: lane
+// 16b + 4j + b (A row 4j + b, k block b) holds piece 4h + j of the container's
+// 16-byte activation pieces, every other lane zeros, so one LDS read serves
+// four chunks.  Chunk 4h + j is accumulated in acc[j], where A row 4j + b
+// gives the sums of tile row 16b + t (column t); acc[j]'s other rows multiply
+// pieces of other chunks and are never read.  So lanes 16j + t hold, in acc[j],
+// chunk j's share of rows 16e + t in element e.
 struct XFromLdsMfma {
   const int8_t* xq;  // LDS, ceil(k/128)*128 bytes
-  mutable u32x4 xw[4] = {};
+  mutable u32x4 xw[2] = {};
   __device__ __forceinline__ void dot(const uint32_t (&d)[5], int c, const uint32_t* lut,
-                                      v4i (&acc)[2]) const {
+                                      v4i (&acc)[4]) const {
     const int lane = threadIdx.x & 63;
-    dot_container_mfma<0>(d, reinterpret_cast<const u32x4*>(xq + c * kTileK),
-                          (lane & 15) == (lane >> 4), xw, lut, acc);
+    const u32x4* xv = reinterpret_cast<const u32x4*>(xq + c * kTileK) + ((lane >> 2) & 3);
+    if ((lane & 3) == (lane >> 4)) {
+      xw[0] = xv[0];
+      xw[1] = xv[4];
+    }
+    dot_container_rows<0>(d, xw[0], lut, acc);
+    dot_container_rows<16>(d, xw[1], lut, acc);
   }
 };
 
@@ -312,8 +346,7 @@ constexpr bool kMfmaSource<XFromLdsMfmaIL> = true;
 // the outstanding loads identical on every path so the compiler waits on
 // exact counts; only the decode is skipped past the end.
 // ring_fill issues the first R containers; ring_run decodes them all.  R is
-// kRing except on lane-interleaved units, whose decode takes a ring of two
-// (kIlRing).
+// kRing or kShortRing.
 template <int R>
 __device__ __forceinline__ void ring_fill(uint32_t (&ring)[R][5], const UnitRun& run) {
   const int lane = threadIdx.x & 63;
@@ -576,7 +609,7 @@ __device__ __forceinline__ void gemv_block(const uint8_t* w_, const X& xsrc, Pre
     }
   } else if constexpr (std::is_same_v<X, XFromLdsMfmaIL>) {
     static_assert(M <= 4, "the lane-interleaved source serves up to four tokens here");
-    uint32_t ring[kIlRing][5];
+    uint32_t ring[kShortRing][5];
     ring_fill(ring, range);
     v4i macc[4] = {};
     ring_run(ring, range, c0, c1, xsrc, lut, macc);
@@ -592,17 +625,26 @@ __device__ __forceinline__ void gemv_block(const uint8_t* w_, const X& xsrc, Pre
     }
   } else if constexpr (kMfmaSource<X>) {
     static_assert(M <= 4 && !kGrp, "the matrix-core sources serve up to four tokens");
-    uint32_t ring[kRing][5];
+    constexpr bool kOne = std::is_same_v<X, XFromLdsMfma>;
+    constexpr int kR = kOne ? kShortRing : kRing;
+    uint32_t ring[kR][5];
     ring_fill(ring, range);
-    v4i macc[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
-    ring_run(ring, range, c0, c1, xsrc, lut, macc);
-    if constexpr (std::is_same_v<X, XFromLdsMfma>) {
-      // lane l < 16 holds rows l, 16 + l, 32 + l, 48 + l of the tile
-      if (lane < 16) {
+    if constexpr (kOne) {
+      v4i macc[4] = {};
+      ring_run(ring, range, c0, c1, xsrc, lut, macc);
+      // rows 16e + t: element e of acc[j] in lanes 16j + t, added over j
+      const int j = lane >> 4;
+      const v4i own = j == 0 ? macc[0] : j == 1 ? macc[1] : j == 2 ? macc[2] : macc[3];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) red[wave * 64 + 16 * e + lane] = macc[0][e] + macc[1][e];
+      for (int e = 0; e < 4; ++e) {
+        int32_t v = own[e];
+        v += __shfl_xor(v, 16, 64);
+        v += __shfl_xor(v, 32, 64);
+        if (lane < 16) red[wave * 64 + 16 * e + lane] = v;
       }
     } else {
+      v4i macc[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+      ring_run(ring, range, c0, c1, xsrc, lut, macc);
       // the LDS of the activations is reused: every wave has finished reading it
       __syncthreads();
 #pragma unroll
