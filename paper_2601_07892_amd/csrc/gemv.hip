@@ -252,15 +252,15 @@ struct XFromLdsMfma {
 // of xq; every other lane's stays zero.  The matrix-core work per container
 // is the same for one to four tokens.
 struct XFromLdsMfmaTok {
-  const int8_t* xq;  // LDS, M rows of kp bytes (zero past k)
-  int kp, m_count;
+  const int8_t* xq;  // LDS, M rows (zero past k), rs bytes apart
+  int rs, m_count;
   mutable u32x4 xw[4] = {};
   __device__ __forceinline__ void dot(const uint32_t (&d)[5], int c, const uint32_t* lut,
                                       v4i (&acc)[2]) const {
     const int lane = threadIdx.x & 63;
     const int m = (lane & 15) - 4 * (lane >> 4);
     const bool own = m >= 0 && m < m_count;
-    dot_container_mfma<0>(d, reinterpret_cast<const u32x4*>(xq + (own ? m : 0) * kp + c * kTileK),
+    dot_container_mfma<0>(d, reinterpret_cast<const u32x4*>(xq + (own ? m : 0) * rs + c * kTileK),
                           own, xw, lut, acc);
   }
   // container c's sums alone, in acc[0]
@@ -270,7 +270,7 @@ struct XFromLdsMfmaTok {
     const int m = (lane & 15) - 4 * (lane >> 4);
     const bool own = m >= 0 && m < m_count;
     dot_container_mfma<0, true>(
-        d, reinterpret_cast<const u32x4*>(xq + (own ? m : 0) * kp + c * kTileK), own, xw, lut,
+        d, reinterpret_cast<const u32x4*>(xq + (own ? m : 0) * rs + c * kTileK), own, xw, lut,
         acc);
   }
 };
@@ -309,18 +309,18 @@ __device__ __forceinline__ void dot_il(const uint32_t (&d)[5], const u32x4 (&xa)
 }
 
 // Activation source of the lane-interleaved units: up to 16 token rows in
-// LDS (kp bytes each, zero past k); lanes 16b + m with m < m_count read token
+// LDS (rs bytes apart, zero past k); lanes 16b + m with m < m_count read token
 // m's chunks b and 4 + b of the container, every other lane keeps zeros.
 struct XFromLdsMfmaIL {
   const int8_t* xq;
-  int kp, m_count;
+  int rs, m_count;
   mutable u32x4 xa[2] = {};
   __device__ __forceinline__ void dot(const uint32_t (&d)[5], int c, const uint32_t* lut,
                                       v4i (&acc)[4]) const {
     const int lane = threadIdx.x & 63;
     const int m = lane & 15, b = lane >> 4;
     if (m < m_count) {
-      const u32x4* xv = reinterpret_cast<const u32x4*>(xq + m * kp + c * kTileK);
+      const u32x4* xv = reinterpret_cast<const u32x4*>(xq + m * rs + c * kTileK);
       xa[0] = xv[b];
       xa[1] = xv[4 + b];
     }
@@ -745,13 +745,18 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Largest M * kp (bytes of staged activations) of the matrix-core int8
+// products: their LDS holds the rows and, after the stream, the partial sums.
+// The rows lie kp + kTokPad bytes apart: kp is a multiple of 128 and mostly of
+// 256, so without the pad the tokens' pieces of one chunk meet in the same
+// banks (a quarter of the LDS's cycles on a LLaMA-3.2-3B step of four tokens).
+constexpr int kTokMaxBytes = 32768;
+constexpr int kTokPad = 64;
+constexpr int kTokLds = kTokMaxBytes + 4 * kTokPad;
+
 // Prelude of the matrix-core int8 products: copies the M activation rows
 // (int8 [M][k], k % 4 == 0) into xq (LDS, rows of kp bytes, zero past k) and
 // reads the tokens' scales.
-// Largest M * kp (bytes of staged activations) of the matrix-core int8
-// products: their LDS holds the rows and, after the stream, the partial sums.
-constexpr int kTokMaxBytes = 32768;
-
 template <int M>
 struct StageRows {
   static constexpr int kPieces = kTokMaxBytes / 16 / kGemvThreads;  // per thread
@@ -787,7 +792,8 @@ struct StageRows {
 #pragma unroll
       for (int e = 0; e < kPieces; ++e) {
         const int i = threadIdx.x + e * kGemvThreads;
-        if (i < M * (kp >> 4)) q16[i] = v[e];
+        const int m = i / (kp >> 4);
+        if (m < M) q16[i + m * (kTokPad >> 4)] = v[e];
       }
     } else {
       const SHERRY_GLOBAL uint32_t* x4 = as_global(reinterpret_cast<const uint32_t*>(x));
@@ -795,7 +801,7 @@ struct StageRows {
       const int k4 = k >> 2, kp4 = kp >> 2;
       for (int i = threadIdx.x; i < M * kp4; i += kGemvThreads) {
         const int m = i / kp4, j = i - m * kp4;
-        q4[i] = j < k4 ? x4[m * k4 + j] : 0u;
+        q4[i + m * (kTokPad >> 2)] = j < k4 ? x4[m * k4 + j] : 0u;
       }
     }
 #pragma unroll
@@ -818,10 +824,10 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_tok_kernel(
     const float* __restrict__ x_scale, WScale ws, const float* __restrict__ gs,
     float* __restrict__ y, int32_t* __restrict__ acc, int64_t n, int64_t k, int split) {
   __shared__ uint32_t lut[32];
-  __shared__ __attribute__((aligned(16))) int8_t xq[kTokMaxBytes];
+  __shared__ __attribute__((aligned(16))) int8_t xq[kTokLds];
   fill_lut(lut);
   const int kp = static_cast<int>((k + kTileK - 1) / kTileK) * kTileK;
-  gemv_block<M, kGrp>(w, XFromLdsMfmaTok{xq, kp, M},
+  gemv_block<M, kGrp>(w, XFromLdsMfmaTok{xq, kp + kTokPad, M},
                       StageRows<M>{x, x_scale, static_cast<int>(k), kp, xq}, ws, y, acc, n,
                       static_cast<int>(k), blockIdx.x, split, lut,
                       reinterpret_cast<int32_t*>(xq), gs, tok_redf(xq));
@@ -832,7 +838,7 @@ __device__ __forceinline__ void tok_batched_block(const sherry_gemm_desc& d, int
                                                   const uint32_t* lut, int8_t* xq) {
   const int k = static_cast<int>(d.k);
   const int kp = ((k + kTileK - 1) / kTileK) * kTileK;
-  gemv_block<M, kGrp>(d.w, XFromLdsMfmaTok{xq, kp, M}, StageRows<M>{d.x, d.x_scale, k, kp, xq},
+  gemv_block<M, kGrp>(d.w, XFromLdsMfmaTok{xq, kp + kTokPad, M}, StageRows<M>{d.x, d.x_scale, k, kp, xq},
                       WScale{d.w_scales, d.w_scale}, d.y, d.acc, d.n, k, g, S, lut,
                       reinterpret_cast<int32_t*>(xq), d.w_group_scales, tok_redf(xq));
 }
@@ -843,7 +849,7 @@ __device__ __forceinline__ void tok_il_batched_block(const sherry_gemm_desc& d, 
                                                      const uint32_t* lut, int8_t* xq) {
   const int k = static_cast<int>(d.k);
   const int kp = ((k + kTileK - 1) / kTileK) * kTileK;
-  gemv_block<M>(d.w, XFromLdsMfmaIL{xq, kp, M}, StageRows<M>{d.x, d.x_scale, k, kp, xq},
+  gemv_block<M>(d.w, XFromLdsMfmaIL{xq, kp + kTokPad, M}, StageRows<M>{d.x, d.x_scale, k, kp, xq},
                 WScale{d.w_scales, d.w_scale}, d.y, d.acc, d.n, k, g, S, lut,
                 reinterpret_cast<int32_t*>(xq));
 }
@@ -853,7 +859,7 @@ __device__ __forceinline__ void tok_il_batched_block(const sherry_gemm_desc& d, 
 __global__ __launch_bounds__(kGemvThreads) void gemv_tok_il_batched_kernel(
     const sherry_gemm_desc* __restrict__ descs, int count, int fold) {
   __shared__ uint32_t lut[32];
-  __shared__ __attribute__((aligned(16))) int8_t xq[kTokMaxBytes];
+  __shared__ __attribute__((aligned(16))) int8_t xq[kTokLds];
   fill_lut(lut);
   const int32_t blk = static_cast<int32_t>(blockIdx.x) >> fold;
   const int lo = find_block_desc(descs, count, blk);
@@ -878,7 +884,7 @@ template <bool kGroups>
 __global__ __launch_bounds__(kGemvThreads) void gemv_tok_batched_kernel(
     const sherry_gemm_desc* __restrict__ descs, int count, int fold) {
   __shared__ uint32_t lut[32];
-  __shared__ __attribute__((aligned(16))) int8_t xq[kTokMaxBytes];
+  __shared__ __attribute__((aligned(16))) int8_t xq[kTokLds];
   fill_lut(lut);
   const int32_t blk = static_cast<int32_t>(blockIdx.x) >> fold;
   const int lo = find_block_desc(descs, count, blk);
