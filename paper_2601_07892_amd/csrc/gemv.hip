@@ -136,24 +136,25 @@ __device__ __forceinline__ void dot_container_lds(const uint32_t (&d)[5], const 
 // activations at xv into xw; the other lanes' xw hold zeros throughout.  Two
 // accumulators take alternate chunks; with kChain one accumulator takes all
 // of them, starting from zero (a container's sum on its own).
-template <int g, bool kChain = false>
+// N chunks (4N codes) per batch of table reads.
+template <int g, int N, bool kChain = false>
 __device__ __forceinline__ void dot_container_mfma(const uint32_t (&d)[5], const u32x4* xv,
-                                                   bool own, u32x4 (&xw)[4], const uint32_t* lut,
+                                                   bool own, u32x4 (&xw)[N], const uint32_t* lut,
                                                    v4i (&acc)[2]) {
   if constexpr (g < 32) {
     __builtin_amdgcn_sched_barrier(0);
     if (own) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) xw[i] = xv[g / 4 + i];
+      for (int i = 0; i < N; ++i) xw[i] = xv[g / 4 + i];
     }
-    uint32_t a4[16];
-    group_offsets<g>(d, a4, std::make_integer_sequence<int, 16>{});
-    uint32_t wv[16];
+    uint32_t a4[4 * N];
+    group_offsets<g>(d, a4, std::make_integer_sequence<int, 4 * N>{});
+    uint32_t wv[4 * N];
 #pragma unroll
-    for (int j = 0; j < 16; ++j)
+    for (int j = 0; j < 4 * N; ++j)
       wv[j] = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(lut) + a4[j]);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < N; ++q) {
       const v4i a = {static_cast<int>(xw[q].x), static_cast<int>(xw[q].y),
                      static_cast<int>(xw[q].z), static_cast<int>(xw[q].w)};
       const v4i b = {static_cast<int>(wv[4 * q]), static_cast<int>(wv[4 * q + 1]),
@@ -165,7 +166,7 @@ __device__ __forceinline__ void dot_container_mfma(const uint32_t (&d)[5], const
         acc[q & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, acc[q & 1], 0, 0, 0);
       }
     }
-    dot_container_mfma<g + 16, kChain>(d, xv, own, xw, lut, acc);
+    dot_container_mfma<g + 4 * N, N, kChain>(d, xv, own, xw, lut, acc);
   }
 }
 
@@ -244,6 +245,11 @@ struct XFromLdsMfma {
   }
 };
 
+// Chunks per batch on the token source: two keep the 4-token kernels at 60
+// registers per lane (74 with four; LLaMA-3.2-3B step at 4 tokens 101.5 ->
+// 100.1 us).
+constexpr int kTokChunks = 2;
+
 // Up to four tokens on the matrix cores, with the same B operand (lane
 // 16b + t holds row 16b + t of the tile): A row 4b + m carries token m's
 // chunk in k block b, so D[4b + m][t] = x_m . w(row 16b + t), and lane
@@ -254,13 +260,13 @@ struct XFromLdsMfma {
 struct XFromLdsMfmaTok {
   const int8_t* xq;  // LDS, M rows (zero past k), rs bytes apart
   int rs, m_count;
-  mutable u32x4 xw[4] = {};
+  mutable u32x4 xw[kTokChunks] = {};
   __device__ __forceinline__ void dot(const uint32_t (&d)[5], int c, const uint32_t* lut,
                                       v4i (&acc)[2]) const {
     const int lane = threadIdx.x & 63;
     const int m = (lane & 15) - 4 * (lane >> 4);
     const bool own = m >= 0 && m < m_count;
-    dot_container_mfma<0>(d, reinterpret_cast<const u32x4*>(xq + (own ? m : 0) * rs + c * kTileK),
+    dot_container_mfma<0, kTokChunks>(d, reinterpret_cast<const u32x4*>(xq + (own ? m : 0) * rs + c * kTileK),
                           own, xw, lut, acc);
   }
   // container c's sums alone, in acc[0]
@@ -269,7 +275,7 @@ struct XFromLdsMfmaTok {
     const int lane = threadIdx.x & 63;
     const int m = (lane & 15) - 4 * (lane >> 4);
     const bool own = m >= 0 && m < m_count;
-    dot_container_mfma<0, true>(
+    dot_container_mfma<0, kTokChunks, true>(
         d, reinterpret_cast<const u32x4*>(xq + (own ? m : 0) * rs + c * kTileK), own, xw, lut,
         acc);
   }
@@ -420,60 +426,67 @@ __device__ __forceinline__ void ring_run_groups(uint32_t (&ring)[kRing][5],
   }
 }
 
+// Containers in flight on the per-group matrix-core source: with two, scales
+// one round ahead and kTokChunks = 2 the grouped kernel takes 76 registers per
+// lane (105 with four, two rounds and four chunks), three workgroups per CU
+// instead of two.  LLaMA-3.2-3B step with per-group scales at 4 tokens 132.9 ->
+// 127.4 us, at 2 tokens 130.8 -> 121.5, 1B at 3 tokens 50.7 -> 47.2.
+constexpr int kGRing = 2;
+
 // Per-group scales on the 4-token matrix-core source: each container's MFMAs
 // run as one chain from zero (slot u of the ring accumulates in pend[u]),
 // and the lane's own row's M token sums (elements 0..M-1) are scaled by the
-// row's group scale into fp32 accumulators (ascending container order) and
-// added to the int32 totals, as in ring_run_groups.  A container is scaled
+// row's group scale into fp32 accumulators (ascending container order) and,
+// with kTotals, added to the int32 totals, as in ring_run_groups.  A container is scaled
 // one step after its MFMAs were issued, once the next container's are in
 // flight, so the chain's latency is not waited for; the walk runs one step
 // past the last container for that (its loads read zeros).
-template <int M, class X>
-__device__ __forceinline__ void ring_run_groups_mfma(uint32_t (&ring)[kRing][5],
-                                                     const UnitRun& run,
+template <int M, bool kTotals, class X>
+__device__ __forceinline__ void ring_run_groups_mfma(const UnitRun& run,
                                                      __amdgpu_buffer_rsrc_t gr, int G, int c0,
                                                      int c1, const X& xsrc, const uint32_t* lut,
                                                      int32_t (&acc)[M], float (&accf)[M]) {
   const int lane = threadIdx.x & 63;
   const int n = c1 - c0;
-  float gring[kRing], gpend[kRing] = {};
-  v4i pend[kRing][2] = {};
+  uint32_t ring[kGRing][5];
+  ring_fill(ring, run);
+  float gring[kGRing], gpend[kGRing] = {};
+  v4i pend[kGRing][2] = {};
 #pragma unroll
-  for (int u = 0; u < kRing; ++u) gring[u] = load_group_scale(gr, G, c0 + u, lane);
-  for (int i = 0; i <= n; i += kRing) {
+  for (int u = 0; u < kGRing; ++u) gring[u] = load_group_scale(gr, G, c0 + u, lane);
+  for (int i = 0; i <= n; i += kGRing) {
 #pragma unroll
-    for (int u = 0; u < kRing; ++u) {
+    for (int u = 0; u < kGRing; ++u) {
       const int j = i + u;
       if (j < n) {
         xsrc.dot_one(ring[u], c0 + j, lut, pend[u]);
         gpend[u] = gring[u];
       }
       // container j - 1, in the previous slot
-      const int pu = (u + kRing - 1) % kRing;  // a constant once unrolled
+      const int pu = (u + kGRing - 1) % kGRing;  // a constant once unrolled
       if (j >= 1 && j <= n) {
 #pragma unroll
         for (int m = 0; m < M; ++m) {
           const int32_t a = pend[pu][0][m];
           accf[m] = __builtin_fmaf(static_cast<float>(a), gpend[pu], accf[m]);
-          acc[m] += a;
+          if constexpr (kTotals) acc[m] += a;
         }
       }
       __builtin_amdgcn_sched_barrier(0);
-      load_unit(ring[u], run, j + kRing, lane);
-      gring[u] = load_group_scale(gr, G, c0 + j + kRing, lane);
+      load_unit(ring[u], run, j + kGRing, lane);
+      gring[u] = load_group_scale(gr, G, c0 + j + kGRing, lane);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
 }
 
-// The same with 16-byte scale loads: a ring of four containers, and lane l
-// reads the scales of its row for four containers at once (one load per
-// round of four, issued two rounds ahead), which touches a quarter of the
-// cache lines of one 4-byte load per container.  Needs every row's scales
+// The same with 16-byte scale loads: lane l reads the scales of its row for
+// four containers at once (one load per round of four, issued a round ahead),
+// which touches a quarter of the cache lines of one 4-byte load per container.  Needs every row's scales
 // 16-byte aligned (G % 4 == 0, gs 16-byte aligned) and c0 % 4 == 0.
-constexpr int kGRing = 4;
 
-template <int M, class X>
+
+template <int M, bool kTotals, class X>
 __device__ __forceinline__ void ring_run_groups_mfma4(const UnitRun& run,
                                                       __amdgpu_buffer_rsrc_t gr, int G, int c0,
                                                       int c1, const X& xsrc, const uint32_t* lut,
@@ -481,42 +494,36 @@ __device__ __forceinline__ void ring_run_groups_mfma4(const UnitRun& run,
   const int lane = threadIdx.x & 63;
   const int n = c1 - c0;
   uint32_t ring[kGRing][5];
-#pragma unroll
-  for (int u = 0; u < kGRing; ++u) {
-    load_unit(ring[u], run, u, lane);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  // scales of rounds 0 and 1 (containers c0 .. c0 + 7 of the lane's row)
-  u32x4 gq0 = __builtin_amdgcn_raw_buffer_load_b128(gr, 4 * (lane * G + c0), 0, 0);
-  u32x4 gq1 = __builtin_amdgcn_raw_buffer_load_b128(gr, 4 * (lane * G + c0 + kGRing), 0, 0);
+  ring_fill(ring, run);
+  // scales of round 0 (containers c0 .. c0 + 3 of the lane's row)
+  u32x4 gnext = __builtin_amdgcn_raw_buffer_load_b128(gr, 4 * (lane * G + c0), 0, 0);
   // sums and scale of the current and the previous container
   float gpend[2] = {0.0f, 0.0f};
   v4i pend[2][2] = {};
-  for (int i = 0; i <= n; i += kGRing) {
-    const u32x4 gcur = gq0;
-    gq0 = gq1;
-    gq1 = __builtin_amdgcn_raw_buffer_load_b128(gr, 4 * (lane * G + c0 + i + 2 * kGRing), 0, 0);
+  for (int i = 0; i <= n; i += 4) {
+    const u32x4 gcur = gnext;
+    gnext = __builtin_amdgcn_raw_buffer_load_b128(gr, 4 * (lane * G + c0 + i + 4), 0, 0);
 #pragma unroll
-    for (int u = 0; u < kGRing; ++u) {
+    for (int u = 0; u < 4; ++u) {
       const int j = i + u;
       if (j < n) {
-        xsrc.dot_one(ring[u], c0 + j, lut, pend[u & 1]);
+        xsrc.dot_one(ring[u % kGRing], c0 + j, lut, pend[u & 1]);
         const uint32_t gbits = gcur[u];  // (a bit cast of the element itself
                                          // reads element 0 with this compiler)
         gpend[u & 1] = __uint_as_float(gbits);
       }
       // container j - 1, in the previous slot
-      const int pu = (u + 1) & 1;  // a constant once unrolled (kGRing is even)
+      const int pu = (u + 1) & 1;  // a constant once unrolled
       if (j >= 1 && j <= n) {
 #pragma unroll
         for (int m = 0; m < M; ++m) {
           const int32_t a = pend[pu][0][m];
           accf[m] = __builtin_fmaf(static_cast<float>(a), gpend[pu], accf[m]);
-          acc[m] += a;
+          if constexpr (kTotals) acc[m] += a;
         }
       }
       __builtin_amdgcn_sched_barrier(0);
-      load_unit(ring[u], run, j + kGRing, lane);
+      load_unit(ring[u % kGRing], run, j + kGRing, lane);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -531,7 +538,7 @@ __device__ __forceinline__ void ring_run_groups_mfma4(const UnitRun& run,
 // y = sx * sum over containers of float(acc_c) * gs[row][c], summed in fp32
 // in container order per wave and then over the S waves in order; redf is
 // LDS for the fp32 partial sums.
-template <int M, bool kGrp = false, class X, class Prelude>
+template <int M, bool kGrp = false, bool kTotals = true, class X, class Prelude>
 __device__ __forceinline__ void gemv_block(const uint8_t* w_, const X& xsrc, Prelude prelude,
                                            WScale ws, float* y, int32_t* acc_out, int64_t n,
                                            int k, int g, int S, const uint32_t* lut,
@@ -592,11 +599,9 @@ __device__ __forceinline__ void gemv_block(const uint8_t* w_, const X& xsrc, Pre
         auto bound = [&](int p) { return p >= S ? C : ((p * C) / S) & ~3; };
         const int b0 = (r < R) ? bound(part) : 0, b1 = (r < R) ? bound(part + 1) : 0;
         const UnitRun run4{w_ + (int64_t(r < R ? r : 0) * C + b0) * kUnitBytes, b1 - b0};
-        ring_run_groups_mfma4<M>(run4, gr, C, b0, b1, xsrc, lut, acc, accf);
+        ring_run_groups_mfma4<M, kTotals>(run4, gr, C, b0, b1, xsrc, lut, acc, accf);
       } else {
-        uint32_t ring[kRing][5];
-        ring_fill(ring, range);
-        ring_run_groups_mfma<M>(ring, range, gr, C, c0, c1, xsrc, lut, acc, accf);
+        ring_run_groups_mfma<M, kTotals>(range, gr, C, c0, c1, xsrc, lut, acc, accf);
       }
       // the LDS of the activations is reused: every wave has finished reading it
       __syncthreads();
@@ -838,7 +843,7 @@ __device__ __forceinline__ void tok_batched_block(const sherry_gemm_desc& d, int
                                                   const uint32_t* lut, int8_t* xq) {
   const int k = static_cast<int>(d.k);
   const int kp = ((k + kTileK - 1) / kTileK) * kTileK;
-  gemv_block<M, kGrp>(d.w, XFromLdsMfmaTok{xq, kp + kTokPad, M}, StageRows<M>{d.x, d.x_scale, k, kp, xq},
+  gemv_block<M, kGrp, !kGrp>(d.w, XFromLdsMfmaTok{xq, kp + kTokPad, M}, StageRows<M>{d.x, d.x_scale, k, kp, xq},
                       WScale{d.w_scales, d.w_scale}, d.y, d.acc, d.n, k, g, S, lut,
                       reinterpret_cast<int32_t*>(xq), d.w_group_scales, tok_redf(xq));
 }
