@@ -9,8 +9,18 @@
 // (16 bytes): every wave load covers whole 512-byte row segments.  A lane
 // turns its block into a code (Eq. 4) and adds the kept magnitudes to its
 // fp64 partial sum.  The codes of 8 units go through LDS, and each unit row's
-// 32 codes are then packed by one lane into its 16-byte head and 4-byte tail,
-// while the next 8 units' loads are in flight.
+// 32 codes are then packed by one lane into its 16-byte head and 4-byte tail.
+//
+// What bounds it is the HBM read of the fp32 weights, as long as the reads
+// never stop: each unit's registers are loaded again, 8 units ahead, as soon
+// as its code is formed, every load and store is issued on every path (past
+// the end through offsets outside their resources), so that the compiler
+// waits for exactly the loads it needs, and the one barrier of a round (the
+// codes are double-buffered) waits for LDS traffic only.  Loading a round's 8
+// units together after the previous round's codes left the memory idle while
+// codes were formed.  4096 x 14336 (with the interleaving of its units) 60.3
+// -> 49.3 us, 8192 x 3072 28.7 -> 24.2, 1024 x 3072 13.6 -> 10.1; 16 units
+// ahead: 50.4, 32.4, 11.6.
 // Rows past n, blocks past k and units past the padded row read as zeros
 // (their offsets fall outside the range of the wave's buffer resource) and so
 // become code 0, the padding code.  The alpha of a row (Eq. 5) adds its 32
@@ -20,7 +30,7 @@
 namespace sherry {
 namespace {
 
-constexpr int kTpRound = 8;  // units in flight per round
+constexpr int kTpRound = 8;  // units in flight per wave, and per round of packing
 
 // Code of one block (Eq. 4): the smallest |w| is dropped (ties to the lowest
 // position); the other three keep their sign, +1 for a kept zero.  Adds the
@@ -59,13 +69,20 @@ __device__ __forceinline__ void tp_pack(const uint8_t* codes, uint32_t (&d)[5],
   (tp_put<js>(d, codes[js]), ...);
 }
 
+// Barrier for LDS traffic only: the weight loads stay in flight.
+__device__ __forceinline__ void tp_lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 template <int ROWS>
 __global__ __launch_bounds__(32 * ROWS) void ternarize_pack_kernel(
     const float* __restrict__ w, int64_t n, int64_t k, uint8_t* __restrict__ out,
     float* __restrict__ alpha) {
-  constexpr int THREADS = 32 * ROWS, WAVES = THREADS / 64;
+  constexpr int WAVES = 32 * ROWS / 64;
   constexpr int QUARTERS = kTileRows / ROWS;  // workgroups per tile
-  __shared__ __attribute__((aligned(16))) uint8_t codes[kTpRound][ROWS][32];
+  __shared__ __attribute__((aligned(16))) uint8_t codes[2][kTpRound][ROWS][32];
   __shared__ double part[ROWS][32];
   const int tid = threadIdx.x;
   const int rl = tid >> 5, j = tid & 31;  // row of the workgroup, block of the unit
@@ -87,36 +104,45 @@ __global__ __launch_bounds__(32 * ROWS) void ternarize_pack_kernel(
   constexpr int kPastRange = 0x7ffffff0;
   double kept = 0.0;
   float4 v[kTpRound];
-  auto load_round = [&](int64_t c0) {
+  auto load = [&](int64_t c) {
+    const int64_t blk = c * 32 + j;
+    const int off = blk < nb ? rowoff + static_cast<int>(blk * 16) : kPastRange;
+    const u32x4 raw = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kLoadStream);
+    return make_float4(__uint_as_float(raw.x), __uint_as_float(raw.y), __uint_as_float(raw.z),
+                       __uint_as_float(raw.w));
+  };
+#pragma unroll
+  for (int u = 0; u < kTpRound; ++u) {
+    v[u] = load(u);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // the tile's units; a lane with nothing to store gets an offset past them
+  const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+      out + tile * C * kUnitBytes, 0, static_cast<int>(C * kUnitBytes), kBufferWord3);
+  const int lane = tid & 63;
+  int buf = 0;
+  for (int64_t c0 = 0; c0 < C; c0 += kTpRound, buf ^= 1) {
 #pragma unroll
     for (int u = 0; u < kTpRound; ++u) {
-      const int64_t blk = (c0 + u) * 32 + j;
-      const int off = blk < nb ? rowoff + static_cast<int>(blk * 16) : kPastRange;
-      const u32x4 raw = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kLoadStream);
-      v[u] = make_float4(__uint_as_float(raw.x), __uint_as_float(raw.y), __uint_as_float(raw.z),
-                         __uint_as_float(raw.w));
+      codes[buf][u][rl][j] = static_cast<uint8_t>(tp_block(v[u], kept));
+      __builtin_amdgcn_sched_barrier(0);
+      v[u] = load(c0 + kTpRound + u);
+      __builtin_amdgcn_sched_barrier(0);
     }
-  };
-  load_round(0);
-  for (int64_t c0 = 0; c0 < C; c0 += kTpRound) {
-#pragma unroll
-    for (int u = 0; u < kTpRound; ++u) codes[u][rl][j] = static_cast<uint8_t>(tp_block(v[u], kept));
-    // the next round's loads fly while this round is packed
-    if (c0 + kTpRound < C) load_round(c0 + kTpRound);
-    __syncthreads();
+    tp_lds_barrier();  // (the one barrier of a round: codes are double-buffered)
     // unit c0 + u, row lane: one lane per unit row packs its 32 codes
-    const int lane = tid & 63;
-    for (int u = wave; u < kTpRound; u += WAVES) {
-      if (lane < ROWS && c0 + u < C) {
-        uint32_t d[5] = {0, 0, 0, 0, 0};
-        tp_pack(codes[u][lane], d, std::make_integer_sequence<int, 32>{});
-        uint8_t* unit = out + (tile * C + c0 + u) * kUnitBytes;
-        const int ri = r0 + lane;
-        *reinterpret_cast<uint4*>(as_global_mut(unit + 16 * ri)) = make_uint4(d[0], d[1], d[2], d[3]);
-        *reinterpret_cast<uint32_t*>(as_global_mut(unit + kHeadBytes + 4 * ri)) = d[4];
-      }
+#pragma unroll
+    for (int i = 0; i < kTpRound / WAVES; ++i) {
+      const int u = wave + i * WAVES;
+      uint32_t d[5] = {0, 0, 0, 0, 0};
+      tp_pack(codes[buf][u][lane & (ROWS - 1)], d, std::make_integer_sequence<int, 32>{});
+      const bool mine = lane < ROWS && c0 + u < C;
+      const int unit = static_cast<int>(c0 + u) * kUnitBytes, ri = r0 + lane;
+      __builtin_amdgcn_raw_buffer_store_b128(u32x4{d[0], d[1], d[2], d[3]}, ro,
+                                             mine ? unit + 16 * ri : kPastRange, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b32(d[4], ro,
+                                            mine ? unit + kHeadBytes + 4 * ri : kPastRange, 0, 0);
     }
-    __syncthreads();  // the next round rewrites codes
   }
   part[rl][j] = kept;
   __syncthreads();
@@ -136,9 +162,14 @@ __global__ __launch_bounds__(32 * ROWS) void ternarize_pack_kernel(
 int launch_ternarize_pack(const float* w, int64_t n, int64_t k, uint8_t* out, float* alpha,
                           hipStream_t s) {
   const int64_t R = ceil_div(n, kTileRows);
-  // rows per workgroup: fewer for matrices with few tiles, so that there are
-  // enough workgroups to spread over the GPU
-  if (R >= 64)
+  // Rows per workgroup.  16 where that puts one or two workgroups on every one
+  // of the 256 CUs (4096 x 14336 49.5 us against 51.5 with 8 rows, 8192 x 2048
+  // 17.9 / 19.5); 8 where it would leave CUs with one more than others, or
+  // more than two per CU (6000 x 6000 35.8 / 33.2, 9000 x 4096 41.8 / 35.3, 14336 x 4096
+  // 55.9 / 50.0, 16384 x 4096 62.8 / 55.7); 4 for matrices with few tiles, so
+  // that there are enough workgroups to spread over the GPU.
+  const int64_t per_cu = ceil_div(4 * R, 256);
+  if (R >= 64 && per_cu <= 2 && 4 * R >= per_cu * 240)
     return launch(ternarize_pack_kernel<16>, dim3(static_cast<unsigned>(4 * R)), dim3(512), 0, s,
                   w, n, k, out, alpha);
   if (R >= 16)
