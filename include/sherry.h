@@ -298,10 +298,10 @@ int sherry_gemv_batched(const sherry_gemv_desc* descs_dev, int count,
 /* ---------------------------------------------------------------------- */
 /* Grouped products: many independent products (any m, e.g. the q, k and  */
 /* v projections of one layer) in one launch: up to 4 tokens each on the   */
-/* matrix-core GEMV (SHERRY_KERNEL_GEMV_TOK), up to 16 (without per-group */
-/* scales) on a 16-token window kernel, else on the register-decoded kernel*/
-/* (SHERRY_KERNEL_SKINNY), which runs token blocks of 32 when every        */
-/* m <= 32 or a descriptor has per-group scales, else of 64.              */
+/* matrix-core GEMV (SHERRY_KERNEL_GEMV_TOK), up to 16 (per-group scales:  */
+/* k % 512 == 0 and aligned) on a 16-token window kernel, else on the      */
+/* register-decoded kernel (SHERRY_KERNEL_SKINNY).  A launch of few blocks */
+/* runs several workgroups per prepared block.                             */
 /* ---------------------------------------------------------------------- */
 
 /* Flag of a grouped launch value: some descriptor has per-group scales. */

@@ -12,7 +12,7 @@ namespace {
 // container are blocks 16p + 4b + c of row 16g + t: four codes side by side in
 // both layouts, so a lane moves eight 20-bit fields, not 32 codes (bound by
 // the launch and one trip to memory and back; with one wave per workgroup and
-// code by code, 7168 units of 4096 x 14336 took 10.4 us; so 5.4).
+// code by code, the 7168 units of 4096 x 14336 took 10.4 us, now 5.4).
 constexpr int kIlWaves = 4;
 
 __global__ __launch_bounds__(64 * kIlWaves) void interleave_kernel(const uint8_t* __restrict__ tiled,
@@ -20,7 +20,7 @@ __global__ __launch_bounds__(64 * kIlWaves) void interleave_kernel(const uint8_t
                                                                    int units) {
   __shared__ __attribute__((aligned(16))) uint32_t u32[kIlWaves][kUnitBytes / 4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int unit = static_cast<int>(blockIdx.x) * kIlWaves + wave;
+  const int64_t unit = static_cast<int64_t>(blockIdx.x) * kIlWaves + wave;
   const size_t base = static_cast<size_t>(unit) * kUnitBytes;
   const bool live = unit < units;
   uint32_t* u = u32[wave];
