@@ -223,13 +223,11 @@ int sherry_gemm_ex(const uint8_t* w, const int8_t* x, const float* x_scale,
                    float w_scale, float* y, int32_t* acc, int64_t m,
                    int64_t n, int64_t k, int kernel, void* stream);
 
-/* The kernel class of a shape, or -SHERRY_E_SHAPE for an invalid shape:
- * SHERRY_KERNEL_GEMV for m <= 4, SHERRY_KERNEL_SKINNY for 5 <= m <= 8192, for
- * k > n and for k >= 3072, else SHERRY_KERNEL_MFMA (longer products with k <=
- * 2048 and k <= n).  SHERRY_KERNEL_AUTO runs the first class on
- * SHERRY_KERNEL_GEMV and both others on SHERRY_KERNEL_SKINNY, whose
- * 128-token workgroups are as fast or faster there than the LDS-tiled
- * kernel; SHERRY_KERNEL_MFMA runs the latter when asked for. */
+/* The kernel sherry_gemm and sherry_gemm_channel run for this shape
+ * (SHERRY_KERNEL_AUTO of sherry_gemm_ex), or -SHERRY_E_SHAPE for an invalid
+ * shape: SHERRY_KERNEL_GEMV for m <= 4, SHERRY_KERNEL_MFMA for m > 8192 with
+ * k <= 1024 and k <= n, else SHERRY_KERNEL_SKINNY (thresholds measured on the
+ * MI355X). */
 int sherry_gemm_kernel_for(int64_t m, int64_t n, int64_t k);
 
 /* sherry_gemm_ex with one weight scale per output channel: the footnote to

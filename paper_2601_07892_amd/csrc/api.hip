@@ -43,9 +43,14 @@ int check_fused(const uint8_t* w, const float* x, const float* x_scale, float* y
 // the register-decoded MFMA kernel (LLaMA-3.2-3B and 8B-scale projections,
 // single launches).
 constexpr int64_t kGemvMaxM = 4;
-// Shape classes of sherry_gemm_kernel_for past that: products of up to
-// kSkinnyMaxLongM tokens, with k > n or with k >= kSkinnyMinLongK, and the rest.
-constexpr int64_t kSkinnyMinLongK = 3072, kSkinnyMaxLongM = 8192;
+// Past that, products of more than kTiledMinM tokens with k <= n and k <=
+// kTiledMaxK run on the LDS-tiled kernel, all others on the register-decoded
+// one, whose workgroups spend about 8 us each besides their units.  Time of the
+// register-decoded kernel over the LDS-tiled one's, k <= n, over 8200 .. 32768
+// tokens x 256 .. 14336 rows: k = 128 0.68 .. 1.84 (mostly 1.0 .. 1.2), 256 ..
+// 512 0.82 .. 1.25, 640 .. 1024 0.71 .. 1.17, 1280 .. 2048 0.71 .. 1.01, 2944 0.65
+// .. 0.87 (16384 x 8192 x 2048: 301 us against 349).
+constexpr int64_t kTiledMinM = 8192, kTiledMaxK = 1024;
 
 int check_product(const uint8_t* w, const int8_t* x, const float* x_scale, float* y,
                   int64_t m, int64_t n, int64_t k, uintptr_t x_align) {
@@ -118,8 +123,8 @@ extern "C" int sherry_quantize_act_batched(const sherry_quant_desc* descs_dev, i
 extern "C" int sherry_gemm_kernel_for(int64_t m, int64_t n, int64_t k) {
   if (!shape_ok(m, n, k)) return -SHERRY_E_SHAPE;
   if (m <= kGemvMaxM) return SHERRY_KERNEL_GEMV;
-  const bool skinny = m <= kSkinnyMaxLongM || k > n || k >= kSkinnyMinLongK;
-  return skinny ? SHERRY_KERNEL_SKINNY : SHERRY_KERNEL_MFMA;
+  const bool tiled = m > kTiledMinM && k <= n && k <= kTiledMaxK;
+  return tiled ? SHERRY_KERNEL_MFMA : SHERRY_KERNEL_SKINNY;
 }
 
 // The descriptor layouts are part of the ABI (Python and C callers build them).
@@ -133,10 +138,7 @@ int gemm_dispatch(const uint8_t* w, const int8_t* x, const float* x_scale, WScal
                   int32_t* acc, int64_t m, int64_t n, int64_t k, int kernel, void* stream) {
   if (kernel == SHERRY_KERNEL_AUTO) {
     const int kk = sherry_gemm_kernel_for(m, n, k);
-    // the register-decoded kernel's 128-token workgroups also serve the longer
-    // products that sherry_gemm_kernel_for sets apart (16384 x 8192 x 2048: 301
-    // us, LDS-tiled 349; 16384 x 2048 x 2048: 85, 86)
-    kernel = kk < 0 ? SHERRY_KERNEL_GEMV : m > kGemvMaxM ? SHERRY_KERNEL_SKINNY : kk;
+    kernel = kk < 0 ? SHERRY_KERNEL_GEMV : kk;  // (an invalid shape is refused below)
   }
   if (kernel == SHERRY_KERNEL_GEMV) {
     int st = check_product(w, x, x_scale, y, m, n, k, 4);

@@ -339,10 +339,14 @@ def test_kernel_choice_by_m():
     for m in (513, 2048, 8192):
         for n, k in ((2048, 2048), (8192, 2048), (2048, 8192), (3072, 3072), (14336, 4096)):
             assert sh.sherry_gemm_kernel_for(m, n, k) == sh.SHERRY_KERNEL_SKINNY
-    # longer products: the LDS-tiled kernel for k <= 2048 and k <= n
+    # longer products: the LDS-tiled kernel for k <= 1024 and k <= n
     for m in (8193, 16384):
-        assert sh.sherry_gemm_kernel_for(m, 2048, 2048) == sh.SHERRY_KERNEL_MFMA
-        assert sh.sherry_gemm_kernel_for(m, 8192, 2048) == sh.SHERRY_KERNEL_MFMA
+        assert sh.sherry_gemm_kernel_for(m, 2048, 128) == sh.SHERRY_KERNEL_MFMA
+        assert sh.sherry_gemm_kernel_for(m, 1024, 1024) == sh.SHERRY_KERNEL_MFMA
+        assert sh.sherry_gemm_kernel_for(m, 8192, 1028) == sh.SHERRY_KERNEL_SKINNY
+        assert sh.sherry_gemm_kernel_for(m, 1020, 1024) == sh.SHERRY_KERNEL_SKINNY
+        assert sh.sherry_gemm_kernel_for(m, 2048, 2048) == sh.SHERRY_KERNEL_SKINNY
+        assert sh.sherry_gemm_kernel_for(m, 8192, 2048) == sh.SHERRY_KERNEL_SKINNY
         assert sh.sherry_gemm_kernel_for(m, 2048, 8192) == sh.SHERRY_KERNEL_SKINNY
         assert sh.sherry_gemm_kernel_for(m, 3072, 3072) == sh.SHERRY_KERNEL_SKINNY
     assert sh.sherry_gemm_kernel_for(0, 2048, 2048) == -sh.SHERRY_E_SHAPE
