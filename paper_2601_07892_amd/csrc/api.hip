@@ -152,7 +152,6 @@ int gemm_dispatch(const uint8_t* w, const int8_t* x, const float* x_scale, WScal
     if (st != SHERRY_OK) return st;
     if (acc && !aligned(acc, 4)) return SHERRY_E_ALIGN;
     return launch_wide(w, x, x_scale, ws, y, acc, m, n, k, as_stream(stream));
-    return launch_wide(w, x, x_scale, ws, y, acc, m, n, k, as_stream(stream));
   }
   if (kernel == SHERRY_KERNEL_MFMA) {
     int st = check_product(w, x, x_scale, y, m, n, k, 16);
