@@ -15,6 +15,7 @@
 // 2048 x 3072 8.8 -> 7.9, 64 x 14336 6.8 -> 5.9, 1000 x 30000 51.7 -> 28.7.
 #include <type_traits>
 
+#include "launch_rules.h"
 #include "sherry_internal.h"
 
 namespace sherry {
@@ -100,7 +101,7 @@ __global__ __launch_bounds__(T) void quantize_rows_kernel(const float* __restric
 }
 
 // Every row of every matrix of a descriptor array, one workgroup per row.
-template <int T, int NV, int AUX>
+template <int T, int NV>
 __global__ __launch_bounds__(T) void quantize_batched_kernel(
     const sherry_quant_desc* __restrict__ descs, int count) {
   __shared__ float part[T / 64];
@@ -118,7 +119,7 @@ __global__ __launch_bounds__(T) void quantize_batched_kernel(
   lo = __builtin_amdgcn_readfirstlane(lo);
   const sherry_quant_desc& d = descs[lo];
   const int64_t row = blk - d.row_begin, k = d.k;
-  quantize_row<T, NV, AUX>(d.x + row * k, k, d.q + row * k, d.x_scale + row, part);
+  quantize_row<T, NV, 0>(d.x + row * k, k, d.q + row * k, d.x_scale + row, part);
 }
 
 // Calls f(T, NV) with the workgroup for rows of up to k values.
@@ -133,14 +134,6 @@ int with_row_shape(int64_t k, F f) {
   return f(integral_constant<int, 512>{}, integral_constant<int, 0>{});
 }
 
-// Inputs of kStreamBytes and more are read past the caches (non-temporal), as
-// they are read once: 8192 x 4096 (134 MB) 32.7 -> 29.2 us, 2048 x 14336 31.0
-// -> 26.9, 512 x 8192 (17 MB) 7.5 -> 6.8, and a LLaMA-3.2-3B layer at 2048
-// tokens, whose inputs follow outputs as large through the caches, 264 -> 257.
-// (A loop over inputs that stay in the Infinity Cache is slower: 2048 x 8192
-// 15.5 -> 17.0.)  Smaller ones are left in the caches.
-constexpr int64_t kStreamBytes = 8 << 20;
-
 }  // namespace
 
 int launch_quantize(const float* x, int64_t m, int64_t k, int8_t* q, float* x_scale,
@@ -148,8 +141,11 @@ int launch_quantize(const float* x, int64_t m, int64_t k, int8_t* q, float* x_sc
   return with_row_shape(k, [&](auto t, auto nv) {
     constexpr int T = decltype(t)::value, NV = decltype(nv)::value;
     const dim3 grid(static_cast<unsigned>(m)), block(T);
-    if (4 * m * k >= kStreamBytes)
-      return launch(quantize_rows_kernel<T, NV, kLoadStream>, grid, block, 0, s, x, k, q, x_scale);
+    // (two passes over a row: the second reads what the first left in the caches)
+    if constexpr (NV > 0) {
+      if (quant_streams(m, k))
+        return launch(quantize_rows_kernel<T, NV, kLoadStream>, grid, block, 0, s, x, k, q, x_scale);
+    }
     return launch(quantize_rows_kernel<T, NV, 0>, grid, block, 0, s, x, k, q, x_scale);
   });
 }
@@ -159,9 +155,9 @@ int launch_quantize_batched(const sherry_quant_desc* descs, int count, int64_t t
   return with_row_shape(max_k, [&](auto t, auto nv) {
     constexpr int T = decltype(t)::value, NV = decltype(nv)::value;
     const dim3 grid(static_cast<unsigned>(total_rows)), block(T);
-    if (4 * total_rows * max_k >= kStreamBytes)
-      return launch(quantize_batched_kernel<T, NV, kLoadStream>, grid, block, 0, s, descs, count);
-    return launch(quantize_batched_kernel<T, NV, 0>, grid, block, 0, s, descs, count);
+    // (the inputs' size is not known here, rows times the longest row only a
+    // bound: never read past the caches)
+    return launch(quantize_batched_kernel<T, NV>, grid, block, 0, s, descs, count);
   });
 }
 

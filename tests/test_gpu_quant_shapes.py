@@ -1,7 +1,8 @@
 """Activation quantization at the row lengths where its workgroup changes (256
-threads holding 2, 4 or 8 pieces each, 512 holding 8 or 16, two passes) and
-where the inputs are read past the caches, lone and grouped, bit-exact against
-the oracle: ragged ends, ties, all-zero rows and a wide range of scales."""
+threads holding 2, 4 or 8 pieces each, 512 holding 8 or 16, two passes), lone
+and grouped, and lone where the inputs are read past the caches (64 MB and
+more), bit-exact against the oracle: ragged ends, ties, all-zero rows and a
+wide range of scales."""
 import sys
 
 import numpy as np
@@ -42,6 +43,22 @@ def test_lone(m, k):
     assert np.array_equal(sx[:m].cpu().numpy(), sx_ref) and float(sx[m]) == -1.0
     assert np.array_equal(q[:m * k].view(m, k).cpu().numpy(), q_ref)
     assert bool((q[m * k:] == 99).all())  # nothing past the last row
+
+
+@pytest.mark.parametrize("k", [1028, 2052, 4100, 8196, 16388, 32772])
+def test_lone_past_the_caches(k):
+    import paper_2601_07892_amd as sh
+    base = _rows(61, k)
+    m = (64 << 20) // (4 * k) + 1
+    print("[case] quant streamed", m, k, file=sys.stderr, flush=True)
+    xd = torch.from_numpy(base).cuda().repeat(-(-m // 61), 1)[:m]
+    q = torch.empty((m, k), dtype=torch.int8, device="cuda")
+    sx = torch.empty(m, dtype=torch.float32, device="cuda")
+    sh.sherry_quantize_act(xd, q, sx)
+    torch.cuda.synchronize()
+    q_ref, sx_ref = (torch.from_numpy(a).cuda() for a in oracle.quantize_act(base))
+    row = torch.arange(m, device="cuda") % 61
+    assert torch.equal(sx, sx_ref[row]) and torch.equal(q, q_ref[row])
 
 
 @pytest.mark.parametrize("k", [1024, 4100, 8196, 16388, 32772])
