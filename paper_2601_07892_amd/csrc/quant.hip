@@ -65,11 +65,16 @@ __device__ __forceinline__ void quantize_row(const float* x, int64_t k, int8_t* 
     amax = block_max<T>(amax, part);
     const float s = amax / 127.0f;
     const float rs = 1.0f / s;
+    // a wave whose whole piece lies past the row skips it: rounding zeros for
+    // nothing costs many short rows 10-20% (16384 x 256 13.8 -> 12.0 us, 10236 x
+    // 104 9.8 -> 8.6)
+    const int first = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x));
 #pragma unroll
     for (int e = 0; e < NV; ++e)
-      __builtin_amdgcn_raw_buffer_store_b32(
-          (amax == 0.0f) ? 0u : quant4(v[e], s, rs), rq,
-          4 * (static_cast<int>(threadIdx.x) + e * T), 0, 0);
+      if (4 * (first + e * T) < static_cast<int>(k))
+        __builtin_amdgcn_raw_buffer_store_b32(
+            (amax == 0.0f) ? 0u : quant4(v[e], s, rs), rq,
+            4 * (static_cast<int>(threadIdx.x) + e * T), 0, 0);
     if (threadIdx.x == 0) *scale = (amax == 0.0f) ? 0.0f : s;
   } else {
     const int64_t k4 = k >> 2;
