@@ -4,8 +4,8 @@
 // its engine accumulates in integers (Appendix A, online phase).  The integer
 // inputs are produced here: s = absmax/127, q = clamp(rint(x/s), -127, 127).
 // One workgroup per token row: 256 threads for rows of up to 8192 values, 512
-// for longer ones.  Rows up to 32768 values are read once into registers;
-// longer rows are read twice (absmax, then quantize).
+// for longer ones (quant_shape).  Rows up to 32768 values are read once into
+// registers; longer rows are read twice (absmax, then quantize).
 //
 // What bounds it: launch and memory latency at decode sizes, HBM at prefill
 // sizes.  A thread's loads go out back to back (the row's end through the
@@ -127,23 +127,32 @@ __global__ __launch_bounds__(T) void quantize_batched_kernel(
   quantize_row<T, NV, 0>(d.x + row * k, k, d.q + row * k, d.x_scale + row, part);
 }
 
-// Calls f(T, NV) with the workgroup for rows of up to k values.
+// Calls f(T, NV) with the workgroup for `rows` rows of up to k values.
 template <class F>
-int with_row_shape(int64_t k, F f) {
+int with_row_shape(int64_t rows, int64_t k, F f) {
   using std::integral_constant;
-  if (k <= 2048) return f(integral_constant<int, 256>{}, integral_constant<int, 2>{});
-  if (k <= 4096) return f(integral_constant<int, 256>{}, integral_constant<int, 4>{});
-  if (k <= 8192) return f(integral_constant<int, 256>{}, integral_constant<int, 8>{});
-  if (k <= 16384) return f(integral_constant<int, 512>{}, integral_constant<int, 8>{});
-  if (k <= 32768) return f(integral_constant<int, 512>{}, integral_constant<int, 16>{});
-  return f(integral_constant<int, 512>{}, integral_constant<int, 0>{});
+  const QuantShape q = quant_shape(rows, k);
+  if (q.threads == 256) {
+    switch (q.pieces) {
+      case 2: return f(integral_constant<int, 256>{}, integral_constant<int, 2>{});
+      case 4: return f(integral_constant<int, 256>{}, integral_constant<int, 4>{});
+      case 8: return f(integral_constant<int, 256>{}, integral_constant<int, 8>{});
+      case 16: return f(integral_constant<int, 256>{}, integral_constant<int, 16>{});
+      default: return f(integral_constant<int, 256>{}, integral_constant<int, 0>{});
+    }
+  }
+  switch (q.pieces) {
+    case 8: return f(integral_constant<int, 512>{}, integral_constant<int, 8>{});
+    case 16: return f(integral_constant<int, 512>{}, integral_constant<int, 16>{});
+    default: return f(integral_constant<int, 512>{}, integral_constant<int, 0>{});
+  }
 }
 
 }  // namespace
 
 int launch_quantize(const float* x, int64_t m, int64_t k, int8_t* q, float* x_scale,
                     hipStream_t s) {
-  return with_row_shape(k, [&](auto t, auto nv) {
+  return with_row_shape(m, k, [&](auto t, auto nv) {
     constexpr int T = decltype(t)::value, NV = decltype(nv)::value;
     const dim3 grid(static_cast<unsigned>(m)), block(T);
     // (two passes over a row: the second reads what the first left in the caches)
@@ -157,7 +166,7 @@ int launch_quantize(const float* x, int64_t m, int64_t k, int8_t* q, float* x_sc
 
 int launch_quantize_batched(const sherry_quant_desc* descs, int count, int64_t total_rows,
                             int64_t max_k, hipStream_t s) {
-  return with_row_shape(max_k, [&](auto t, auto nv) {
+  return with_row_shape(total_rows, max_k, [&](auto t, auto nv) {
     constexpr int T = decltype(t)::value, NV = decltype(nv)::value;
     const dim3 grid(static_cast<unsigned>(total_rows)), block(T);
     // (the inputs' size is not known here, rows times the longest row only a

@@ -20,6 +20,9 @@ int main() {
     for (int64_t v; in >> v;) a.push_back(v);
     if (fn == "quant_streams") {
       std::printf("%d\n", quant_streams(a[0], a[1]) ? 1 : 0);
+    } else if (fn == "quant_shape") {
+      const QuantShape q = quant_shape(a[0], a[1]);
+      std::printf("%d %d\n", q.threads, q.pieces);
     } else {
       std::fprintf(stderr, "unknown query: %s\n", fn.c_str());
       return 1;

@@ -82,3 +82,27 @@ def test_grouped(k):
         q_ref, sx_ref = oracle.quantize_act(x)
         assert np.array_equal(sx.cpu().numpy(), sx_ref)
         assert np.array_equal(q.cpu().numpy(), q_ref)
+
+
+@pytest.mark.parametrize("k", [8196, 16388])
+def test_grouped_many_rows(k):
+    # one long row among 2^23 short ones: 512 threads per row would not fit a grid
+    import paper_2601_07892_amd as sh
+    print("[case] quant many rows", k, file=sys.stderr, flush=True)
+    long_row, base, m = _rows(1, k), _rows(61, 4), 1 << 23
+    xs = [torch.from_numpy(long_row).cuda(),
+          torch.from_numpy(base).cuda().repeat(-(-m // 61), 1)[:m].contiguous()]
+    qs = [torch.empty(x.shape, dtype=torch.int8, device="cuda") for x in xs]
+    sxs = [torch.full((x.shape[0],), -1.0, device="cuda") for x in xs]
+    descs = (sh.sherry_quant_desc * 2)()
+    for d, x, q, sx in zip(descs, xs, qs, sxs):
+        d.x, d.q, d.x_scale = x.data_ptr(), q.data_ptr(), sx.data_ptr()
+        d.m, d.k = x.shape
+    rows, mk = sh.sherry_quantize_act_batched_prepare(descs)
+    sh.sherry_quantize_act_batched(torch.from_numpy(sh.descs_to_bytes(descs)).cuda(), 2, rows, mk)
+    torch.cuda.synchronize()
+    row = torch.arange(m, device="cuda") % 61
+    for (q, sx), (ref, pick) in zip(zip(qs, sxs), ((long_row, None), (base, row))):
+        q_ref, sx_ref = (torch.from_numpy(a).cuda() for a in oracle.quantize_act(ref))
+        assert torch.equal(q, q_ref if pick is None else q_ref[pick])
+        assert torch.equal(sx, sx_ref if pick is None else sx_ref[pick])
