@@ -493,7 +493,7 @@ extern "C" int sherry_gemm_batched_prepare(sherry_gemm_desc* descs, int count,
   const int32_t sel = grouped && mm > 32 ? 32 : (mm < 17 ? 17 : mm);
   const int64_t tokens = wide_batched_tokens(sel);
   const int st = assign_blocks(descs, count, [&](const sherry_gemm_desc& d) {
-    return int64_t(wide_blocks(d.n, d.w_group_scales != nullptr)) * ceil_div(d.m, tokens);
+    return wide_blocks(d.n, d.w_group_scales != nullptr) * ceil_div(d.m, tokens);
   }, total_blocks);
   if (st != SHERRY_OK) return st;
   *max_m = sel | (grouped ? SHERRY_LAUNCH_GROUPS : 0);

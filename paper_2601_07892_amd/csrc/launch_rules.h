@@ -7,6 +7,8 @@
 
 namespace sherry {
 
+constexpr int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
 // Activation quantization: inputs of kStreamBytes and more are read past the
 // caches (non-temporal).  Usually the operation before has just written the
 // input.  Time with streaming against without, after a kernel that wrote x from
@@ -28,6 +30,197 @@ constexpr QuantShape quant_shape(int64_t rows, int64_t k) {
   if (k <= 8192) return {256, k <= 2048 ? 2 : k <= 4096 ? 4 : 8};
   if (rows * 512 > int64_t(UINT32_MAX)) return {256, k <= 16384 ? 16 : 0};
   return {512, k <= 16384 ? 8 : k <= 32768 ? 16 : 0};
+}
+
+// ---- register-decoded products: shapes of a workgroup -----------------------
+
+// Tokens x 64-row tiles of a workgroup, and the parts its tiles' K is split in.
+enum WideShape : int {
+  kWideLong, kWideMid, kWideHalf, kWideQuarter, kWideShort, kWideTiny, kWidePair, kWideThin
+};
+// Estimated time (us) of a launch: the busiest CU runs c workgroups of U units
+// per wave; a lone workgroup takes fix + lat U, bound by one wave's chain, and c
+// of them base + c (thr U + o).  Fitted to measured launches (m 37-8192, n
+// 300-14336, k 128-14336), which it orders right or within 5% of the best.
+struct WideCost {
+  int tokens, tiles, parts;
+  float fix, lat, base, thr, o;
+};
+constexpr WideCost kWideCost[] = {
+    {128, 4, 1, 8.2f, 0.68f, 5.0f, 0.64f, 7.7f},   // long
+    {64, 4, 1, 6.0f, 0.54f, 5.0f, 0.45f, 1.7f},    // mid
+    {64, 2, 2, 6.0f, 0.575f, 5.0f, 0.50f, 2.0f},   // half
+    {64, 2, 4, 7.5f, 0.83f, 5.0f, 0.80f, 5.2f},    // quarter (eight waves)
+    {32, 1, 4, 5.0f, 0.55f, 4.0f, 0.41f, 1.1f},    // short
+    {32, 1, 8, 5.3f, 0.83f, 4.0f, 0.78f, 3.06f},   // tiny (eight waves)
+    {32, 2, 2, 5.0f, 0.55f, 4.0f, 0.50f, 1.1f},    // pair (grouped launches)
+    {32, 4, 1, 5.5f, 0.46f, 4.0f, 0.46f, 1.5f},    // thin (grouped launches)
+};
+// The shapes with per-group scales (long, quarter and thin are not offered).
+constexpr WideCost kWideGroupCost[] = {
+    {},
+    {64, 4, 1, 5.9f, 0.77f, 4.0f, 0.625f, 3.9f},   // mid
+    {64, 2, 2, 5.8f, 0.83f, 4.0f, 0.78f, 1.2f},    // half
+    {},
+    {32, 1, 4, 5.0f, 0.71f, 4.0f, 0.60f, 0.3f},    // short
+    {32, 1, 8, 5.6f, 1.07f, 4.0f, 1.05f, 3.1f},    // tiny (eight waves)
+    {32, 2, 2, 4.6f, 0.67f, 4.0f, 0.46f, 0.6f},    // pair
+    {},
+};
+// `workgroups` of rows of `units` units; a part is whole chunks of `chunk` units.
+constexpr float wide_estimate(const WideCost& c, int64_t workgroups, int64_t units,
+                              int64_t chunk = 1) {
+  const float u = static_cast<float>(ceil_div(ceil_div(units, c.parts), chunk) * chunk);
+  const float per = static_cast<float>(ceil_div(workgroups, 256));
+  const float one = c.fix + c.lat * u, many = c.base + per * (c.thr * u + c.o);
+  return one > many ? one : many;
+}
+// The offer with the lowest estimate.
+struct WidePick {
+  int best = -1;
+  float t = 0.0f;
+  constexpr void offer(int shape, float e) {
+    if (best < 0 || e < t) t = e, best = shape;
+  }
+};
+
+// A lone product.
+constexpr int wide_pick(int64_t m, int64_t n, int64_t k) {
+  WidePick q{};
+  for (int i : {kWideLong, kWideMid, kWideHalf, kWideQuarter, kWideShort, kWideTiny}) {
+    const WideCost& c = kWideCost[i];
+    q.offer(i, wide_estimate(c, ceil_div(ceil_div(n, 64), c.tiles) * ceil_div(m, c.tokens),
+                             ceil_div(k, 128)));
+  }
+  return q.best;
+}
+// With per-group scales (pieces: read 16 bytes, four units, at a time).
+constexpr int wide_pick_group(int64_t m, int64_t n, int64_t k, bool pieces) {
+  WidePick q{};
+  for (int i : {kWideMid, kWideHalf, kWidePair, kWideShort, kWideTiny}) {
+    const WideCost& c = kWideGroupCost[i];
+    q.offer(i, wide_estimate(c, ceil_div(ceil_div(n, 64), c.tiles) * ceil_div(m, c.tokens),
+                             ceil_div(k, 128), pieces ? 4 : 1));
+  }
+  return q.best;
+}
+
+// Prepared blocks of a grouped launch: 8 tiles (4 with per-group scales) x 32
+// tokens when the launch value is at most 32, else 8 tiles x 64 tokens.
+constexpr int64_t wide_blocks(int64_t n, bool group_scales) {
+  return ceil_div(ceil_div(n, 64), group_scales ? 4 : 8);
+}
+constexpr int wide_batched_tokens(int max_m) { return max_m <= 32 ? 32 : 64; }
+
+// Shapes of the grouped launches.  A launch knows its blocks, its number of
+// products and its longest m, not its products' rows: the lines are drawn for
+// products of one row length (the projections of one input), and where a mix of
+// lengths (1 to 112 units) would run far longer on the shape that is best for
+// those, they give way.  Figures: mean time over the best shape's, products of one
+// length / mixed, about 100 launches each.
+//
+// 8 x 64 blocks.  By the cost model, at 24 units a row.  An odd last token block is
+// priced for 128 x 4: one workgroup runs both halves of its tiles in series, 64
+// tokens of each idle (129 .. 256 blocks: 128 x 4 1.53 / 2.9 with an odd one, 1.03 /
+// 1.75 without; 64 x 4 1.00 / 1.5 and 1.03 / 1.45).  64 x 2 only up to 128 blocks
+// (past that up to 1.3 times the launch before these shapes).
+constexpr int64_t kWideUnits = 24;
+constexpr int wide_pick_batched(int64_t total_blocks, int max_m) {
+  const int64_t tb = ceil_div(max_m, 64);
+  const WideCost& l = kWideCost[kWideLong];
+  WidePick q{};
+  q.offer(kWideLong, wide_estimate(l, ceil_div(total_blocks * ((tb + 1) / 2 * 2), tb), kWideUnits) +
+                         (tb % 2 ? l.lat * kWideUnits : 0.0f));
+  q.offer(kWideMid, wide_estimate(kWideCost[kWideMid], 2 * total_blocks, kWideUnits));
+  if (total_blocks <= 128) {
+    q.offer(kWideHalf, wide_estimate(kWideCost[kWideHalf], 4 * total_blocks, kWideUnits));
+    q.offer(kWideShort, wide_estimate(kWideCost[kWideShort], 16 * total_blocks, kWideUnits));
+  }
+  return q.best;
+}
+// 8 x 32 blocks.  65 .. 96: 32 x 1 1.18 / 1.00 (32 x 2 1.01 / 1.53); 97 .. 192: 32
+// x 2 1.02 / 1.5 (32 x 1 1.4 / 1.00, and slower than the launch before these
+// shapes); 193 and more: 32 x 4 1.00 (32 x 2 1.13 .. 1.27).
+constexpr int wide_pick_batched32(int64_t total_blocks) {
+  return total_blocks <= 96 ? kWideShort : total_blocks <= 192 ? kWidePair : kWideThin;
+}
+// 4 x 32 blocks of products with per-group scales.  Up to 128: 32 x 1 1.00 .. 1.05 /
+// 1.00 (32 x 2 1.2 .. 1.02 / 1.4); 129 .. 384: 32 x 2 1.02 / 1.27 (32 x 1 1.2 ..
+// 1.46 / 1.02, with one length up to 1.2 times the launch before these shapes);
+// 385 .. 768: 32 x 2 1.13 / 1.06 (64 x 2 1.06 / 1.26, mixed up to 1.28 times the
+// launch before; 64 x 4 1.01 .. 1.24 / 1.7); 769 .. 1536: 64 x 4 1.03 / 1.35 for the
+// few projections of one input, 64 x 2 1.08 / 1.09 for more products; past that
+// 64 x 4 1.01 / 1.15 (64 x 2 1.08 / 1.04).  The 64-token shapes take two blocks at a
+// time, which launches of fewer than 32 tokens do not have: half of their work
+// would be idle.
+constexpr int wide_pick_batched_group(int64_t total_blocks, int count, int max_m) {
+  if (total_blocks <= 128) return kWideShort;
+  if (total_blocks <= 768 || max_m < 32) return kWidePair;
+  return total_blocks <= 1536 && count > 3 ? kWideHalf : kWideMid;
+}
+
+// What a workgroup of a grouped launch runs: tile groups g, g + step, ..
+// (reps of them, one after the other; those past the tiles are left out) of the
+// tokens from t0; reps = 0: nothing.
+struct WideRun {
+  int g, reps, step;
+  int64_t t0;
+  bool odd;  // an odd last token block, where the kernel has a shape for it
+};
+
+// Block lb of a product of R tiles and m tokens, part sub of its workgroups,
+// each of `tiles` tiles.  8 x 64 blocks; with 128 tokens every two blocks of one
+// tile group (an even and the next token block) are run by two workgroups of
+// four tiles each.
+constexpr WideRun wide_run64(int tokens, int tiles, int lb, int sub, int64_t m, int R) {
+  const int gb = (R + 7) / 8;  // tile groups of a prepared block
+  WideRun r{0, 1, 1, 0, false};
+  if (tokens <= 64) {
+    const int rpb = 8 / tiles;  // workgroups along the rows
+    const int tb = lb / gb;
+    r.t0 = int64_t(tb) * 64 + sub / rpb * tokens;
+    r.g = (lb - tb * gb) * rpb + sub % rpb;
+  } else {
+    const int T = static_cast<int>((m + 63) / 64);
+    const int pairs = T / 2 * 2 * gb;  // blocks of the paired token blocks
+    const bool paired = lb < pairs;
+    const int q = paired ? lb : 2 * (lb - pairs);  // the last, odd token block: both
+    r.reps = paired ? 1 : 2;                       // halves of its tiles
+    const int pr = paired ? q / (2 * gb) : T / 2;
+    r.g = paired ? q - pr * 2 * gb : q;
+    r.t0 = int64_t(pr) * 128;
+  }
+  if (r.t0 >= m) r.reps = 0;
+  return r;
+}
+
+// 8 x 32 blocks, run by `per` workgroups each.
+constexpr WideRun wide_run32(int tiles, int per, int lb, int sub, int64_t m, int R) {
+  const int gb = (R + 7) / 8, tb = lb / gb, rpb = 8 / tiles;
+  return {(lb - tb * gb) * rpb + sub, int64_t(tb) * 32 < m ? rpb / per : 0, per, int64_t(tb) * 32,
+          false};
+}
+
+// 4 x 32 blocks of a product with per-group scales, run by `per` workgroups each.
+// 64 tokens take two token blocks at a time: with four tiles the first half of a
+// product's blocks run them, with two tiles each block takes half of the tiles.
+// There an odd last token block is run block by block, by a 32 x 4 shape (both
+// halves of its tiles in series took the launch up to 1.6 times as long).
+constexpr WideRun wide_run32_group(int tokens, int tiles, int per, int lb, int sub, int64_t m,
+                                   int R) {
+  const int gb = (R + 3) / 4, tb = lb / gb;
+  WideRun r{lb - tb * gb, 1, 1, int64_t(tb) * tokens, false};
+  if (tokens == 32) {
+    const int rpb = 4 / tiles;
+    r = {r.g * rpb + sub, rpb / per, per, int64_t(tb) * 32, false};
+  } else if (tiles == 2) {
+    const int pairs = static_cast<int>((m + 31) / 64) * 2 * gb;  // blocks of the paired token blocks
+    r.odd = lb >= pairs;
+    r.g = r.odd ? lb - pairs : lb % (2 * gb);
+    r.t0 = int64_t(lb / (2 * gb)) * 64;
+  }
+  if (r.t0 >= m) r.reps = 0;
+  return r;
 }
 
 }  // namespace sherry

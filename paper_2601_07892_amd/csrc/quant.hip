@@ -15,7 +15,6 @@
 // 2048 x 3072 8.8 -> 7.9, 64 x 14336 6.8 -> 5.9, 1000 x 30000 51.7 -> 28.7.
 #include <type_traits>
 
-#include "launch_rules.h"
 #include "sherry_internal.h"
 
 namespace sherry {

@@ -9,6 +9,7 @@
 #include <utility>
 
 #include "../../include/sherry.h"
+#include "launch_rules.h"
 
 namespace sherry {
 
@@ -23,8 +24,6 @@ constexpr int kUnit2Bytes = 1024;
 // Unit of the 1.67-bit layout: 64 rows x 96 weights (32 codes of three
 // weights per row), stored like a 5-bit unit (1280 bytes).
 constexpr int kTileK3 = 96;
-
-constexpr int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Decode kernel work split.  A workgroup has kGemvWaves waves; the
 // containers of a 64-row tile are split among S waves of one workgroup,
@@ -292,8 +291,6 @@ int launch_wide(const uint8_t* w, const int8_t* x, const float* x_scale, WScale 
                 int32_t* acc, int64_t m, int64_t n, int64_t k, hipStream_t s);
 int launch_wide_group(const uint8_t* w, const int8_t* x, const float* x_scale, const float* gs,
                       float* y, int32_t* acc, int64_t m, int64_t n, int64_t k, hipStream_t s);
-int wide_blocks(int64_t n, bool group_scales);
-int wide_batched_tokens(int max_m);
 int launch_wide_batched(const sherry_gemm_desc* descs, int count, int64_t total_blocks,
                         int max_m, bool groups, hipStream_t s);
 int launch_gemv_batched(const sherry_gemv_desc* descs, int count,

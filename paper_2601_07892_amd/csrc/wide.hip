@@ -586,67 +586,64 @@ __global__ __launch_bounds__(G::THREADS) __attribute__((amdgpu_waves_per_eu(G::E
   wd_block<G>(p, blockIdx.x, lds);
 }
 
-// Grouped launch.  A prepared block is 8 tiles x 64 tokens of its product
-// (token blocks outermost); it is run by 8 / TILES x 64 / TOK workgroups, or,
-// with 128-token blocks, every two prepared blocks of one tile group (an even
-// and the next token block) by two workgroups of four tiles each.
+// Grouped launch of 8 x 64 blocks, PER workgroups each (wide_run64).
 template <class G>
 __global__ __launch_bounds__(G::THREADS) __attribute__((amdgpu_waves_per_eu(G::EU))) void wide_batched_kernel(
     const sherry_gemm_desc* __restrict__ descs, int count) {
   __shared__ __attribute__((aligned(16))) int8_t lds[G::LDS];
-  constexpr int PER = G::PER;
-  const int32_t blk = static_cast<int32_t>(blockIdx.x) / PER;
-  const int sub = static_cast<int>(blockIdx.x) % PER;
+  static_assert(G::TOK <= 64 || (G::TOK == 128 && G::TILES == 4 && G::PER == 1),
+                "two prepared blocks, two workgroups");
+  const int32_t blk = static_cast<int32_t>(blockIdx.x) / G::PER;
   const int lo = find_block_desc(descs, count, blk);
   if (lo < 0) return;
   const sherry_gemm_desc& d = descs[lo];
-  const int lb = blk - d.block_begin;
   const int R = (d.n + kTileRows - 1) / kTileRows;
-  const int gb = (R + 7) / 8;  // tile groups of a prepared block
-  int g, reps = 1;
-  int64_t t0;
-  if constexpr (G::TOK <= 64) {
-    constexpr int RPB = 8 / G::TILES;  // workgroups along the rows
-    const int tb = lb / gb;
-    t0 = int64_t(tb) * 64 + sub / RPB * G::TOK;
-    g = (lb - tb * gb) * RPB + sub % RPB;
-  } else {
-    static_assert(G::TOK == 128 && G::TILES == 4 && PER == 1, "two prepared blocks, two workgroups");
-    const int T = (d.m + 63) / 64;
-    const int pairs = T / 2 * 2 * gb;  // blocks of the paired token blocks
-    const bool paired = lb < pairs;
-    const int q = paired ? lb : 2 * (lb - pairs);  // the last, odd token block: both
-    reps = paired ? 1 : 2;                         // halves of its tiles
-    const int pr = paired ? q / (2 * gb) : T / 2;
-    g = paired ? q - pr * 2 * gb : q;
-    t0 = int64_t(pr) * 128;
-  }
-  if (t0 >= d.m) return;
+  const WideRun run = wide_run64(G::TOK, G::TILES, blk - d.block_begin,
+                                 static_cast<int>(blockIdx.x) % G::PER, d.m, R);
+  if (run.reps == 0) return;
   WdProblem p{d.w, d.x, d.x_scale, d.y, d.acc, d.n, d.k, d.m, WScale{d.w_scales, d.w_scale}, nullptr};
-  wd_tokens<G>(p, t0);
-  for (int h = 0; h < reps; ++h) {
-    if ((g + h) * G::TILES >= R) return;
+  wd_tokens<G>(p, run.t0);
+  for (int h = 0; h < run.reps; ++h) {
+    if ((run.g + h) * G::TILES >= R) return;
     if (h) __syncthreads();  // the table, scales and strips are written again
-    wd_block<G>(p, g + h, lds);
+    wd_block<G>(p, run.g + h, lds);
   }
 }
 
 // Grouped launch of 32-token prepared blocks (every m <= 32, or some product
 // with per-group scales): 8 tiles x 32 tokens of a product without per-group
-// scales, on G0; 4 tiles x 32 tokens of one with them, on G1 (void: none).
-// PER workgroups share a block's parts.  A G1 of 64 tokens takes two blocks at
-// a time: four tiles by the first of two blocks (the others return), or two
-// tiles by each of them, an odd last one both its halves.
-template <class G0_, class G1_, int PER_>
+// scales, on G0 (wide_run32); 4 tiles x 32 tokens of one with them, on G1 (void:
+// none), and its odd last token block on G1O where G1 has 64 tokens x two tiles
+// (wide_run32_group).  PER workgroups share a block's parts.
+template <class G0_, class G1_, int PER_, class G1O_ = void>
 struct WdShort32 {
   using G0 = G0_;
-  static constexpr bool kGroups = !std::is_same_v<G1_, void>;
+  static constexpr bool kGroups = !std::is_same_v<G1_, void>, kOdd = !std::is_same_v<G1O_, void>;
   using GG = std::conditional_t<kGroups, G1_, G0>;
+  using GO = std::conditional_t<kOdd, G1O_, GG>;
   static constexpr int PER = PER_;
   static constexpr int THREADS = G0::THREADS, EU = G0::EU < GG::EU ? G0::EU : GG::EU;
-  static constexpr int LDS = G0::LDS > GG::LDS ? G0::LDS : GG::LDS;
-  static_assert(G0::TOK == 32 && G0::THREADS == GG::THREADS, "one block size");
+  static constexpr int LDS0 = G0::LDS > GG::LDS ? G0::LDS : GG::LDS;
+  static constexpr int LDS = LDS0 > GO::LDS ? LDS0 : GO::LDS;
+  static_assert(G0::TOK == 32 && G0::THREADS == GG::THREADS && G0::THREADS == GO::THREADS,
+                "one block size");
+  static_assert(8 / G0::TILES % PER == 0, "parts of a block");
+  static_assert(!kGroups || (GG::TOK == 64 ? PER == 1 : 4 / GG::TILES % PER == 0),
+                "parts of a block (64 tokens: one workgroup)");
+  static_assert(kOdd == (kGroups && GG::TOK == 64 && GG::TILES == 2), "an odd token block's shape");
+  static_assert(!kOdd || (GO::TOK == 32 && GO::TILES == 4), "a whole prepared block");
 };
+
+template <class G>
+__device__ __forceinline__ void wd_run(WdProblem& p, const WideRun& run, int R, int8_t* lds) {
+  wd_tokens<G>(p, run.t0);
+  for (int h = 0; h < run.reps; ++h) {
+    const int g = run.g + h * run.step;
+    if (g * G::TILES >= R) return;
+    if (h) __syncthreads();  // the table, scales and strips are written again
+    wd_block<G>(p, g, lds);
+  }
+}
 
 template <class B>
 __global__ __launch_bounds__(B::THREADS) __attribute__((amdgpu_waves_per_eu(B::EU))) void wide_batched32_kernel(
@@ -660,59 +657,24 @@ __global__ __launch_bounds__(B::THREADS) __attribute__((amdgpu_waves_per_eu(B::E
   const int lo = find_block_desc(descs, count, blk);
   if (lo < 0) return;
   const sherry_gemm_desc& d = descs[lo];
-  const int lb = blk - d.block_begin;
   const int R = (d.n + kTileRows - 1) / kTileRows;
   WdProblem p{d.w, d.x, d.x_scale, d.y, d.acc, d.n, d.k, d.m, WScale{d.w_scales, d.w_scale},
               d.w_group_scales};
   if constexpr (B::kGroups) {
     if (d.w_group_scales) {
-      const int gb = (R + 3) / 4, T = (d.m + 31) / 32;
-      int g, reps, step = 1, tb;
-      if constexpr (G1::TOK == 32) {
-        constexpr int RPB = 4 / G1::TILES;
-        static_assert(RPB % PER == 0, "parts of a block");
-        tb = lb / gb;
-        g = (lb - tb * gb) * RPB + sub;
-        reps = RPB / PER;
-        step = PER;
-      } else if constexpr (G1::TILES == 4) {
-        static_assert(PER == 1, "one workgroup per two blocks");
-        tb = lb / gb;
-        g = lb - tb * gb;
-        reps = 1;
-      } else {
-        static_assert(G1::TILES == 2 && PER == 1, "half of the tiles of two blocks");
-        const int pairs = T / 2 * 2 * gb;
-        const bool paired = lb < pairs;
-        const int q = paired ? lb : 2 * (lb - pairs);
-        reps = paired ? 1 : 2;
-        tb = paired ? q / (2 * gb) : T / 2;
-        g = paired ? q - tb * 2 * gb : q;
-      }
-      const int64_t t0 = int64_t(tb) * G1::TOK;
-      if (t0 >= d.m) return;
+      const WideRun run =
+          wide_run32_group(G1::TOK, G1::TILES, PER, blk - d.block_begin, sub, d.m, R);
+      if (run.reps == 0) return;
       p.acc = nullptr;
-      wd_tokens<G1>(p, t0);
-      for (int h = 0; h < reps; ++h) {
-        if ((g + h * step) * G1::TILES >= R) return;
-        if (h) __syncthreads();  // the table, scales and strips are written again
-        wd_block<G1>(p, g + h * step, lds);
+      if constexpr (B::kOdd) {
+        if (run.odd) return wd_run<typename B::GO>(p, run, R, lds);
       }
-      return;
+      return wd_run<G1>(p, run, R, lds);
     }
   }
-  constexpr int RPB = 8 / G0::TILES;
-  static_assert(RPB % PER == 0, "parts of a block");
-  const int gb = (R + 7) / 8, tb = lb / gb;
-  const int64_t t0 = int64_t(tb) * 32;
-  if (t0 >= d.m) return;
-  wd_tokens<G0>(p, t0);
-  for (int h = 0; h < RPB / PER; ++h) {
-    const int g = (lb - tb * gb) * RPB + sub + h * PER;
-    if (g * G0::TILES >= R) return;
-    if (h) __syncthreads();
-    wd_block<G0>(p, g, lds);
-  }
+  const WideRun run = wide_run32(G0::TILES, PER, blk - d.block_begin, sub, d.m, R);
+  if (run.reps == 0) return;
+  wd_run<G0>(p, run, R, lds);
 }
 
 constexpr int64_t kWdMaxGridY = 32768;  // further token blocks go to further launches
@@ -746,26 +708,15 @@ using WdTiny = WdCfg<1, 8, 8, 2>;    // 32 x 1, K in 8, eight waves
 using WdPair = WdCfg<1, 2, 4, 3>;    // 32 x 2, K in 2 (grouped launches)
 using WdThin = WdCfg<1, 1, 4, 4>;    // 32 x 4 (grouped launches)
 
-// Estimated time (us) of a launch on one of them: the busiest CU runs c
-// workgroups of U units per wave; a lone workgroup takes fix + lat U, bound
-// by one wave's chain, and c of them base + c (thr U + o).  Fitted to
-// measured launches (m 37-8192, n 300-14336, k 128-14336), which it orders
-// right or within 5% of the best.
-struct WdCost {
-  float fix, lat, base, thr, o;
-};
-constexpr WdCost kWdLong{8.2f, 0.68f, 5.0f, 0.64f, 7.7f}, kWdMid{6.0f, 0.54f, 5.0f, 0.45f, 1.7f},
-    kWdHalf{6.0f, 0.575f, 5.0f, 0.50f, 2.0f}, kWdQuarter{7.5f, 0.83f, 5.0f, 0.80f, 5.2f},
-    kWdShort{5.0f, 0.55f, 4.0f, 0.41f, 1.1f}, kWdTiny{5.3f, 0.83f, 4.0f, 0.78f, 3.06f},
-    kWdPair{5.0f, 0.55f, 4.0f, 0.50f, 1.1f}, kWdThin{5.5f, 0.46f, 4.0f, 0.46f, 1.5f};
 template <class G>
-float wd_estimate(const WdCost& c, int64_t workgroups, int64_t units) {
-  const int64_t part = ceil_div(units, G::S);
-  const float U = static_cast<float>(G::GR == 4 ? (part + 3) / 4 * 4 : part);
-  const float per = static_cast<float>(ceil_div(workgroups, 256));
-  const float one = c.fix + c.lat * U, many = c.base + per * (c.thr * U + c.o);
-  return one > many ? one : many;
+constexpr bool wd_is(const WideCost& c) {
+  return c.tokens == G::TOK && c.tiles == G::TILES && c.parts == G::S;
 }
+static_assert(wd_is<WdLong>(kWideCost[kWideLong]) && wd_is<WdMid>(kWideCost[kWideMid]) &&
+                  wd_is<WdHalf>(kWideCost[kWideHalf]) && wd_is<WdQuarter>(kWideCost[kWideQuarter]) &&
+                  wd_is<WdShort>(kWideCost[kWideShort]) && wd_is<WdTiny>(kWideCost[kWideTiny]) &&
+                  wd_is<WdPair>(kWideCost[kWidePair]) && wd_is<WdThin>(kWideCost[kWideThin]),
+              "the shapes that the cost model prices");
 
 // The shapes with per-group scales: twice the accumulators (int32 sums of one
 // unit, fp32 sums), and a conversion and an fma per unit and sum (128 VALU
@@ -781,34 +732,22 @@ template <int GR>
 using WdGrpShort = WdCfg<1, 4, 4, 3, GR>;  // 32 x 1, K in 4
 template <int GR>
 using WdGrpTiny = WdCfg<1, 8, 8, 2, GR>;  // 32 x 1, K in 8, eight waves
-constexpr WdCost kWdGrpMid{5.9f, 0.77f, 4.0f, 0.625f, 3.9f}, kWdGrpHalf{5.8f, 0.83f, 4.0f, 0.78f, 1.2f},
-    kWdGrpPair{4.6f, 0.67f, 4.0f, 0.46f, 0.6f}, kWdGrpShort{5.0f, 0.71f, 4.0f, 0.60f, 0.3f},
-    kWdGrpTiny{5.6f, 1.07f, 4.0f, 1.05f, 3.1f};
-
-// The offer with the lowest estimate (ids from 0).
-struct WdPick {
-  int best = -1;
-  float t = 0.0f;
-  void offer(int id, float e) {
-    if (best < 0 || e < t) t = e, best = id;
-  }
-};
+template <int GR>
+using WdGrpThin = WdCfg<1, 1, 4, 3, GR>;  // 32 x 4 (an odd token block beside 64 x 2)
+static_assert(wd_is<WdGrpMid<1>>(kWideGroupCost[kWideMid]) &&
+                  wd_is<WdGrpHalf<1>>(kWideGroupCost[kWideHalf]) &&
+                  wd_is<WdGrpPair<1>>(kWideGroupCost[kWidePair]) &&
+                  wd_is<WdGrpShort<1>>(kWideGroupCost[kWideShort]) &&
+                  wd_is<WdGrpTiny<1>>(kWideGroupCost[kWideTiny]),
+              "the shapes that the cost model prices");
 
 template <int GR>
 int launch_wide_group_gr(const WdProblem& p, hipStream_t s) {
-  const int64_t R = ceil_div(p.n, kTileRows), C = ceil_div(p.k, kTileK), m = p.m;
-  auto blocks = [&](int64_t tiles, int64_t tok) { return ceil_div(R, tiles) * ceil_div(m, tok); };
-  WdPick k;
-  k.offer(0, wd_estimate<WdGrpMid<GR>>(kWdGrpMid, blocks(4, 64), C));
-  k.offer(1, wd_estimate<WdGrpHalf<GR>>(kWdGrpHalf, blocks(2, 64), C));
-  k.offer(2, wd_estimate<WdGrpPair<GR>>(kWdGrpPair, blocks(2, 32), C));
-  k.offer(3, wd_estimate<WdGrpShort<GR>>(kWdGrpShort, blocks(1, 32), C));
-  k.offer(4, wd_estimate<WdGrpTiny<GR>>(kWdGrpTiny, blocks(1, 32), C));
-  switch (k.best) {
-    case 0: return launch_wide_cfg<WdGrpMid<GR>>(p, s);
-    case 1: return launch_wide_cfg<WdGrpHalf<GR>>(p, s);
-    case 2: return launch_wide_cfg<WdGrpPair<GR>>(p, s);
-    case 3: return launch_wide_cfg<WdGrpShort<GR>>(p, s);
+  switch (wide_pick_group(p.m, p.n, p.k, GR == 4)) {
+    case kWideMid: return launch_wide_cfg<WdGrpMid<GR>>(p, s);
+    case kWideHalf: return launch_wide_cfg<WdGrpHalf<GR>>(p, s);
+    case kWidePair: return launch_wide_cfg<WdGrpPair<GR>>(p, s);
+    case kWideShort: return launch_wide_cfg<WdGrpShort<GR>>(p, s);
     default: return launch_wide_cfg<WdGrpTiny<GR>>(p, s);
   }
 }
@@ -819,16 +758,13 @@ int launch_wide_batched_cfg(const sherry_gemm_desc* descs, int count, int64_t to
   return launch(wide_batched_kernel<G>, dim3(static_cast<unsigned>(total_blocks * G::PER)),
                 dim3(G::THREADS), 0, s, descs, count);
 }
-template <class G0, class G1, int PER>
+template <class G0, class G1, int PER, class G1O = void>
 int launch_wide_batched32_cfg(const sherry_gemm_desc* descs, int count, int64_t total_blocks,
                               hipStream_t s) {
-  return launch(wide_batched32_kernel<WdShort32<G0, G1, PER>>,
+  return launch(wide_batched32_kernel<WdShort32<G0, G1, PER, G1O>>,
                 dim3(static_cast<unsigned>(total_blocks * PER)), dim3(G0::THREADS), 0, s, descs,
                 count);
 }
-
-// The rows' lengths are not known at a grouped launch: 24 units stand for them.
-constexpr int64_t kWdUnits = 24;
 
 }  // namespace
 
@@ -836,21 +772,12 @@ int launch_wide(const uint8_t* w, const int8_t* x, const float* x_scale, WScale 
                 int32_t* acc, int64_t m, int64_t n, int64_t k, hipStream_t s) {
   const WdProblem p{w, x, x_scale, y, acc, static_cast<int>(n), static_cast<int>(k),
                     static_cast<int>(m), ws, nullptr};
-  const int64_t R = ceil_div(n, kTileRows), C = ceil_div(k, kTileK);
-  auto blocks = [&](int64_t tiles, int64_t tok) { return ceil_div(R, tiles) * ceil_div(m, tok); };
-  WdPick q;
-  q.offer(0, wd_estimate<WdLong>(kWdLong, blocks(4, 128), C));
-  q.offer(1, wd_estimate<WdMid>(kWdMid, blocks(4, 64), C));
-  q.offer(2, wd_estimate<WdHalf>(kWdHalf, blocks(2, 64), C));
-  q.offer(3, wd_estimate<WdQuarter>(kWdQuarter, blocks(2, 64), C));
-  q.offer(4, wd_estimate<WdShort>(kWdShort, blocks(1, 32), C));
-  q.offer(5, wd_estimate<WdTiny>(kWdTiny, blocks(1, 32), C));
-  switch (q.best) {
-    case 0: return launch_wide_cfg<WdLong>(p, s);
-    case 1: return launch_wide_cfg<WdMid>(p, s);
-    case 2: return launch_wide_cfg<WdHalf>(p, s);
-    case 3: return launch_wide_cfg<WdQuarter>(p, s);
-    case 4: return launch_wide_cfg<WdShort>(p, s);
+  switch (wide_pick(m, n, k)) {
+    case kWideLong: return launch_wide_cfg<WdLong>(p, s);
+    case kWideMid: return launch_wide_cfg<WdMid>(p, s);
+    case kWideHalf: return launch_wide_cfg<WdHalf>(p, s);
+    case kWideQuarter: return launch_wide_cfg<WdQuarter>(p, s);
+    case kWideShort: return launch_wide_cfg<WdShort>(p, s);
     default: return launch_wide_cfg<WdTiny>(p, s);
   }
 }
@@ -868,49 +795,33 @@ int launch_wide_group(const uint8_t* w, const int8_t* x, const float* x_scale, c
   return pieces ? launch_wide_group_gr<4>(p, s) : launch_wide_group_gr<1>(p, s);
 }
 
-// Prepared blocks of a grouped launch: 8 tiles (4 with per-group scales) x 32
-// tokens when max_m <= 32, else 8 tiles x 64 tokens.
-int wide_blocks(int64_t n, bool group_scales) {
-  return static_cast<int>(ceil_div(ceil_div(n, kTileRows), group_scales ? 4 : 8));
-}
-int wide_batched_tokens(int max_m) { return max_m <= 32 ? 32 : 64; }
-
 int launch_wide_batched(const sherry_gemm_desc* descs, int count, int64_t total_blocks,
                         int max_m, bool groups, hipStream_t s) {
-  WdPick q;
   if (groups) {
     // (a launch's products may have any row lengths: 4-byte scale loads)
-    q.offer(0, wd_estimate<WdGrpMid<1>>(kWdGrpMid, ceil_div(total_blocks, 2), kWdUnits));
-    q.offer(1, wd_estimate<WdGrpHalf<1>>(kWdGrpHalf, total_blocks, kWdUnits));
-    q.offer(2, wd_estimate<WdGrpPair<1>>(kWdGrpPair, total_blocks * 2, kWdUnits));
-    q.offer(3, wd_estimate<WdGrpShort<1>>(kWdGrpShort, total_blocks * 4, kWdUnits));
-    switch (q.best) {
-      case 0: return launch_wide_batched32_cfg<WdPair, WdGrpMid<1>, 1>(descs, count, total_blocks, s);
-      case 1: return launch_wide_batched32_cfg<WdPair, WdGrpHalf<1>, 1>(descs, count, total_blocks, s);
-      case 2: return launch_wide_batched32_cfg<WdPair, WdGrpPair<1>, 2>(descs, count, total_blocks, s);
-      default: return launch_wide_batched32_cfg<WdPair, WdGrpShort<1>, 4>(descs, count, total_blocks, s);
+    switch (wide_pick_batched_group(total_blocks, count, max_m)) {
+      case kWideMid:
+        return launch_wide_batched32_cfg<WdThin, WdGrpMid<1>, 1>(descs, count, total_blocks, s);
+      case kWideHalf:
+        return launch_wide_batched32_cfg<WdThin, WdGrpHalf<1>, 1, WdGrpThin<1>>(descs, count,
+                                                                               total_blocks, s);
+      case kWidePair:
+        return launch_wide_batched32_cfg<WdThin, WdGrpPair<1>, 2>(descs, count, total_blocks, s);
+      default:
+        return launch_wide_batched32_cfg<WdPair, WdGrpShort<1>, 4>(descs, count, total_blocks, s);
     }
   }
   if (max_m <= 32) {
-    q.offer(0, wd_estimate<WdThin>(kWdThin, total_blocks * 2, kWdUnits));
-    q.offer(1, wd_estimate<WdPair>(kWdPair, total_blocks * 4, kWdUnits));
-    q.offer(2, wd_estimate<WdShort>(kWdShort, total_blocks * 8, kWdUnits));
-    switch (q.best) {
-      case 0: return launch_wide_batched32_cfg<WdThin, void, 2>(descs, count, total_blocks, s);
-      case 1: return launch_wide_batched32_cfg<WdPair, void, 4>(descs, count, total_blocks, s);
+    switch (wide_pick_batched32(total_blocks)) {
+      case kWideThin: return launch_wide_batched32_cfg<WdThin, void, 2>(descs, count, total_blocks, s);
+      case kWidePair: return launch_wide_batched32_cfg<WdPair, void, 4>(descs, count, total_blocks, s);
       default: return launch_wide_batched32_cfg<WdShort, void, 8>(descs, count, total_blocks, s);
     }
   }
-  // (64 tokens of a 128-token workgroup's are idle in an odd last block)
-  const int64_t T = ceil_div(max_m, 64);
-  q.offer(0, wd_estimate<WdLong>(kWdLong, ceil_div(total_blocks * ((T + 1) / 2 * 2), T), kWdUnits));
-  q.offer(1, wd_estimate<WdMid>(kWdMid, total_blocks * WdMid::PER, kWdUnits));
-  q.offer(2, wd_estimate<WdHalf>(kWdHalf, total_blocks * WdHalf::PER, kWdUnits));
-  q.offer(3, wd_estimate<WdShort>(kWdShort, total_blocks * WdShort::PER, kWdUnits));
-  switch (q.best) {
-    case 0: return launch_wide_batched_cfg<WdLong>(descs, count, total_blocks, s);
-    case 1: return launch_wide_batched_cfg<WdMid>(descs, count, total_blocks, s);
-    case 2: return launch_wide_batched_cfg<WdHalf>(descs, count, total_blocks, s);
+  switch (wide_pick_batched(total_blocks, max_m)) {
+    case kWideLong: return launch_wide_batched_cfg<WdLong>(descs, count, total_blocks, s);
+    case kWideMid: return launch_wide_batched_cfg<WdMid>(descs, count, total_blocks, s);
+    case kWideHalf: return launch_wide_batched_cfg<WdHalf>(descs, count, total_blocks, s);
     default: return launch_wide_batched_cfg<WdShort>(descs, count, total_blocks, s);
   }
 }

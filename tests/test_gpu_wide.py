@@ -76,16 +76,17 @@ def test_lone(dev, m, n, k, channel):
 
 
 # (m, n, k) of the products of one launch, by prepared blocks (8 tiles x 64
-# tokens): up to 32, 64, 128 and more; odd and even numbers of token blocks,
+# tokens): up to 32, 64, 128, 256 and more; odd and even numbers of token blocks,
 # one token, a single tile, ragged rows
 FEW = [(33, 70, 132), (64, 1030, 260), (129, 300, 1540), (1, 64, 128)]
 MORE = FEW + [(128, 4100, 132), (257, 520, 388)]
 MANY = MORE + [(700, 1030, 260), (64, 16390, 136)]
 MOST = MANY + [(257, 4100, 132), (129, 2052, 516)]
+LONGEST = MOST + [(1090, 7000, 132), (193, 1030, 4)]
+GROUPED = [(FEW, 1, 32), (MORE, 33, 64), (MANY, 65, 128), (MOST, 129, 256), (LONGEST, 385, 512)]
 
 
-@pytest.mark.parametrize("shapes,low,high", [(FEW, 1, 32), (MORE, 33, 64), (MANY, 65, 128),
-                                             (MOST, 129, 256)])
+@pytest.mark.parametrize("shapes,low,high", GROUPED)
 @pytest.mark.parametrize("channel", [False, True])
 def test_grouped(dev, shapes, low, high, channel):
     import paper_2601_07892_amd as sh
@@ -185,17 +186,22 @@ def test_lone_group_infinite_scale_stays_in_its_group(dev):
 # (m, n, k, per-group) of the products of one launch; prepared blocks of 8
 # tiles (4 with per-group scales) x 32 tokens
 SMALL32 = [(17, 70, 132, False), (32, 1030, 1540, False), (5, 300, 260, False)]
+MIXED32 = [(33, 70, 132, True), (300, 4100, 260, True), (65, 520, 1540, False), (97, 1000, 388, True)]
 GROUPED32 = [
     (SMALL32, 1, 96),
-    (SMALL32 + [(20, 51000, 68, False)], 97, 128),
+    (SMALL32 + [(20, 51000, 68, False)], 97, 192),
     (SMALL32 + [(31, 86000, 68, False)], 161, 192),
+    (SMALL32 + [(31, 98000, 68, False)], 193, 256),
+    ([(33, 70, 132, True), (17, 130, 1540, False), (5, 1030, 260, True), (1, 64, 128, True)], 1, 64),
     ([(33, 70, 132, True), (64, 1030, 260, True), (129, 300, 1540, True), (1, 64, 128, True)], 1, 192),
-    ([(33, 70, 132, True), (300, 4100, 260, True), (65, 520, 1540, False), (97, 1000, 388, True)], 193,
-     256),
+    (MIXED32, 193, 256),
     ([(33, 70, 132, True), (500, 4100, 260, True), (65, 520, 644, False), (97, 1000, 388, True)], 257,
      384),
     ([(33, 70, 132, True), (700, 4100, 260, True), (65, 520, 644, False), (97, 1000, 388, True)], 385,
      512),
+    # odd and even last token blocks of 32 under 64-token workgroups
+    (MIXED32 + [(1030, 5000, 132, True), (64, 130, 4, True), (31, 300, 260, True)], 769, 1536),
+    (MIXED32 + [(2050, 5130, 132, True), (64, 130, 4, True), (31, 300, 260, True)], 1537, 2048),
 ]
 
 
