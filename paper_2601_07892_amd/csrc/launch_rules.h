@@ -32,6 +32,30 @@ constexpr QuantShape quant_shape(int64_t rows, int64_t k) {
   return {512, k <= 16384 ? 8 : k <= 32768 ? 16 : 0};
 }
 
+// ---- 5-16-token window kernel: K in four parts ------------------------------
+
+// Grouped launches of up to kSmFoldBlocks prepared blocks (of four tiles) run
+// four workgroups per block, each of one tile with a quarter of its K per wave,
+// for the products whose rows gain by it (sm_splits); the blocks of the others are
+// run by one of the four, one tile per wave.  Time over whole rows at 12 tokens,
+// rows of 1 / 4 / 8 / 16 / 32 / 64 units: up to 64 blocks 1.06 / 0.89 / 0.75 / 0.58 /
+// 0.48 / 0.41 (18.2 -> 7.5 us), left whole 1.00; 128 blocks 1.17 / 1.01 / 0.85 / 0.69
+// / 0.61 / 0.56 (two workgroups per CU, one round); 192 blocks 1.74 / 1.43 / 1.22 /
+// 0.99 / 0.91 / 0.87, left whole 1.15 .. 1.28; 256 blocks 1.80 / 1.57 / 1.38 / 1.16 /
+// 1.07 / 1.00.  (Launches that mix long rows with short ones gain more: 158 blocks
+// 47 -> 19 us.)  Per-group scales: parts of whole chunks of four units.
+constexpr int64_t kSmFoldBlocks = 192;
+constexpr bool sm_splits(int64_t units, int64_t blocks, bool group_scales) {
+  return units >= (blocks > 128 ? 8 : 4) + (group_scales ? 4 : 0);
+}
+// The workgroup of a block's four that runs it whole.  Workgroups go to the 8 XCDs
+// in turn and there to the four shader engines in turn, so the choice varies with
+// both (always the first: 184 blocks 20 -> 44 us).
+constexpr int sm_whole_sub(int block) {
+  const int j = block >> 1;
+  return (j ^ (j >> 2) ^ (j >> 4)) & 3;
+}
+
 // ---- register-decoded products: shapes of a workgroup -----------------------
 
 // Tokens x 64-row tiles of a workgroup, and the parts its tiles' K is split in.

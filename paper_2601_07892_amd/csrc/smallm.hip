@@ -59,12 +59,6 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 constexpr int kSmWaves = 4;
 constexpr int kSmThreads = 64 * kSmWaves;
 constexpr int kSmTok = 16;                      // token rows staged
-// Prepared blocks up to which K is split over the waves: 4 x 256 workgroups
-// are two per CU (66 KB of LDS each) and two rounds.  Past that every CU has
-// a workgroup that walks whole rows, and the split only adds rounds: 216
-// blocks 43 -> 28 us, 432 blocks even (-3% .. +3%), eight layers of 1616 / 3456
-// (352 blocks) 24 -> 31, 864 blocks 47 -> 66.
-constexpr int64_t kSmFoldBlocks = 256;
 constexpr int kSmRing = 4;                      // units per wave in the register ring
 
 // Staging geometry with each tile's K in S parts: a window is UPW units of
@@ -429,7 +423,8 @@ __device__ __forceinline__ void sm_block(const SmProblem& p, int g, uint32_t* lu
 // kGroups: some descriptor carries per-group scales (a kernel of its own,
 // so that the other keeps its registers).  A prepared block is four tiles, one
 // per wave; with S = 4 it is run by four workgroups, each of one tile with a
-// quarter of its K per wave.
+// quarter of its K per wave, or, where the rows are short, by one of them as with
+// S = 1.
 template <class CFG, bool kGroups, bool kIL>
 constexpr int kSmPerSimd = CFG::S > 1 ? 2 : kIL ? 6 : kGroups ? 3 : 4;
 
@@ -447,6 +442,16 @@ smallm_batched_kernel(
   const sherry_gemm_desc& d = descs[lo];
   const SmProblem p{d.w, d.x, d.x_scale, d.y, d.acc, d.n, d.k, d.m,
                     WScale{d.w_scales, d.w_scale}, d.w_group_scales};
+  if constexpr (CFG::S > 1) {
+    const bool grp = kGroups && p.gs;
+    if (!sm_splits((p.k + kTileK - 1) / kTileK, gridDim.x / CFG::S, grp)) {
+      if (static_cast<int>(blockIdx.x) % CFG::S != sm_whole_sub(blk)) return;
+      const int g = blk - d.block_begin;
+      if (grp) sm_block<SmCfg<1>, kGroups>(p, g, lut, stages, zrow, xs);
+      else sm_block<SmCfg<1>, false, kIL>(p, g, lut, stages, zrow, xs);
+      return;
+    }
+  }
   // S = 4: tile 4 (blk - begin) + blockIdx % 4
   const int g = static_cast<int>(blockIdx.x) - d.block_begin * CFG::S;
   if (CFG::S > 1 && g * kTileRows >= p.n) return;

@@ -79,6 +79,10 @@ int main() {
     } else if (fn == "quant_shape") {
       const QuantShape q = quant_shape(a[0], a[1]);
       std::printf("%d %d\n", q.threads, q.pieces);
+    } else if (fn == "sm_splits") {
+      std::printf("%d\n", a[1] <= kSmFoldBlocks && sm_splits(a[0], a[1], a[2] != 0) ? 1 : 0);
+    } else if (fn == "sm_whole_sub") {
+      std::printf("%d\n", sm_whole_sub(static_cast<int>(a[0])));
     } else if (fn == "wide_pick") {
       std::printf("%d\n", wide_pick(a[0], a[1], a[2]));
     } else if (fn == "wide_pick_group") {

@@ -1,8 +1,10 @@
 """Grouped launches of 5 to 16 tokens with few blocks, whose tiles' K is split
-over the four waves of a workgroup: on both sides of the block count where the
-split ends, products of one unit per row (parts without units), of 5 units
-(parts of 2, 2, 1 and 0), of 17 (two windows per part) and of 4-byte-aligned
-rows; ragged last tiles and blocks.  int32 sums bit-exact against the oracle,
+over the four waves of a workgroup where the rows are long enough: on both sides
+of the block counts where that line moves and where the split ends, products of
+one unit per row, of 5 units (parts of 2, 2, 1 and 0), of 8 and 12 (split or
+whole by the blocks; with per-group scales parts of 4, 4 and 0), of 17 (two
+windows per part) and of 4-byte-aligned rows, split and whole ones in one
+launch; ragged last tiles and blocks.  int32 sums bit-exact against the oracle,
 fp32 outputs bit-identical to its epilogue (per-group scales: within the
 fp32-sum bound)."""
 import sys
@@ -24,7 +26,7 @@ def dev():
     return d
 
 
-@pytest.mark.parametrize("total", [9, 256, 257])
+@pytest.mark.parametrize("total", [9, 128, 129, 192, 193, 257])
 @pytest.mark.parametrize("call", ["tiled", "il", "group"])
 @pytest.mark.parametrize("m", [5, 16])
 def test_split_k(dev, total, call, m):
@@ -32,8 +34,8 @@ def test_split_k(dev, total, call, m):
     print("[case] smallm split", total, call, m, file=sys.stderr, flush=True)
     group = call == "group"
     # the last product fills the launch up to `total` blocks of 256 rows
-    shapes = ([(70, 512), (130, 2560), (257, 1536)] if group else
-              [(70, 128), (130, 644), (257, 2176), (3, 132)])
+    shapes = ([(70, 512), (130, 2560), (257, 1536), (66, 1024)] if group else
+              [(70, 128), (130, 644), (257, 2176), (3, 132), (66, 1024), (130, 1536)])
     used = sum(-(-n // 256) for n, _ in shapes)
     shapes.append((256 * (total - used) - 63, 512))
     descs = (sh.sherry_gemm_desc * len(shapes))()

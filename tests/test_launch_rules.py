@@ -27,6 +27,21 @@ def test_quantization_workgroups_cover_rows_and_fit_the_grid():
         assert threads == (256 if k <= 8192 or m >= 1 << 23 else 512), (m, k)
 
 
+def test_window_kernel_splits_only_rows_that_gain():
+    # (units, blocks, per-group scales)
+    cases = [(1, 9, 0), (3, 128, 0), (4, 128, 0), (4, 9, 1), (8, 9, 1), (7, 129, 0), (8, 192, 0),
+             (8, 192, 1), (12, 192, 1), (12, 193, 0), (112, 256, 0)]
+    assert [v for v, in ask(*(("sm_splits",) + c for c in cases))] == [0, 0, 1, 0, 1, 0, 1, 0, 1, 0, 0]
+
+
+def test_whole_rows_spread_over_the_gpu():
+    # workgroup b goes to XCD b % 8 and there, in turn, to one of four engines
+    subs = [v for v, in ask(*(("sm_whole_sub", b) for b in range(256)))]
+    b = [4 * blk + sub for blk, sub in enumerate(subs)]
+    places = [(v % 8, v // 8 % 4) for v in b]
+    assert len(set(places)) == 32 and max(map(places.count, set(places))) <= 2 * 256 // 32
+
+
 # blocks of a grouped launch, shape, workgroups per block, and the most tile
 # groups that one workgroup may run in series
 LAUNCHES = [(64, LONG, 1, 2), (64, MID, 2, 1), (64, HALF, 4, 1), (64, SHORT, 16, 1),
