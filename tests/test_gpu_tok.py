@@ -400,3 +400,38 @@ def test_interleave_after_gpu_ternarize(dev):
     t = sh.sherry_unpack(packed.cpu().numpy(), n, k)
     assert np.array_equal(il.cpu().numpy(), sh.sherry_pack_il(t))
     assert np.array_equal(sh.sherry_unpack_il(il.cpu().numpy(), n, k), t)
+
+
+@pytest.mark.parametrize("units", [1, 2, 3, 5, 6, 7, 13, 61])
+@pytest.mark.parametrize("n", [1, 66])
+def test_group_scales_end_inside_a_piece(dev, units, n):
+    # rows of no whole 16-byte piece of scales, 4-byte aligned, with NaN behind
+    # them: the last row's last piece reaches past the matrix and is cut there
+    import paper_2601_07892_amd as sh
+    print("[case] tok group ragged", units, n, file=sys.stderr, flush=True)
+    k = 128 * units - 4
+    gs = (np.random.default_rng(units).random((n, units)) + 0.01).astype(np.float32)
+    buf = torch.full((gs.size + 9,), float("nan"), dtype=torch.float32, device=dev)
+    gsd = buf[1:1 + gs.size].view(n, units)
+    gsd.copy_(torch.from_numpy(gs))
+    t = synth.ternary_34(n, k, 8, "tokragged", units)
+    w = torch.from_numpy(sh.sherry_pack(t)).to(dev)
+    for m in (1, 2, 3, 4):
+        q, sx = oracle.quantize_act(synth.activations(m, k, 8, "tokragged", m))
+        qd, sxd = torch.from_numpy(q).to(dev), torch.from_numpy(sx).to(dev)
+        ys = [torch.full((m, n), float("nan"), dtype=torch.float32, device=dev) for _ in range(2)]
+        acc = torch.empty((m, n), dtype=torch.int32, device=dev)
+        sh.sherry_gemm_group(w, qd, sxd, gsd, ys[0], acc, m, n, k, sh.SHERRY_KERNEL_GEMV_TOK)
+        descs = (sh.sherry_gemm_desc * 1)()
+        d = descs[0]
+        d.w, d.x, d.x_scale, d.y = w.data_ptr(), qd.data_ptr(), sxd.data_ptr(), ys[1].data_ptr()
+        d.acc, d.w_group_scales, d.n, d.k, d.m = None, gsd.data_ptr(), n, k, m
+        total, value = sh.sherry_gemm_batched_prepare(descs)
+        assert value == m | sh.SHERRY_LAUNCH_GROUPS
+        sh.sherry_gemm_batched(torch.from_numpy(sh.descs_to_bytes(descs)).to(dev), 1, total, value)
+        torch.cuda.synchronize()
+        y_ref, mag, acc_ref = oracle.product_groups(q, t, sx, gs, threads=16)
+        assert np.array_equal(acc.cpu().numpy(), acc_ref)
+        for y in ys:
+            err = np.abs(y.cpu().numpy().astype(np.float64) - y_ref)
+            assert (err <= (units + 4) * 2.0 ** -24 * mag).all()
