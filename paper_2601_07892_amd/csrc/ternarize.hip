@@ -120,8 +120,19 @@ __global__ __launch_bounds__(32 * ROWS) void ternarize_pack_kernel(
   const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
       out + tile * C * kUnitBytes, 0, static_cast<int>(C * kUnitBytes), kBufferWord3);
   const int lane = tid & 63;
+  // packs unit c of the round in codes[buf]: one lane per unit row, its 32 codes
+  auto pack = [&](int buf, int u, int64_t c) {
+    uint32_t d[5] = {0, 0, 0, 0, 0};
+    tp_pack(codes[buf][u][lane & (ROWS - 1)], d, std::make_integer_sequence<int, 32>{});
+    const int unit = static_cast<int>(c) * kUnitBytes, ri = r0 + lane;
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4{d[0], d[1], d[2], d[3]}, ro,
+                                           lane < ROWS ? unit + 16 * ri : kPastRange, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(
+        d[4], ro, lane < ROWS ? unit + kHeadBytes + 4 * ri : kPastRange, 0, 0);
+  };
   int buf = 0;
-  for (int64_t c0 = 0; c0 < C; c0 += kTpRound, buf ^= 1) {
+  int64_t c0 = 0;
+  for (; c0 + kTpRound <= C; c0 += kTpRound, buf ^= 1) {
 #pragma unroll
     for (int u = 0; u < kTpRound; ++u) {
       codes[buf][u][rl][j] = static_cast<uint8_t>(tp_block(v[u], kept));
@@ -130,19 +141,20 @@ __global__ __launch_bounds__(32 * ROWS) void ternarize_pack_kernel(
       __builtin_amdgcn_sched_barrier(0);
     }
     tp_lds_barrier();  // (the one barrier of a round: codes are double-buffered)
-    // unit c0 + u, row lane: one lane per unit row packs its 32 codes
 #pragma unroll
-    for (int i = 0; i < kTpRound / WAVES; ++i) {
-      const int u = wave + i * WAVES;
-      uint32_t d[5] = {0, 0, 0, 0, 0};
-      tp_pack(codes[buf][u][lane & (ROWS - 1)], d, std::make_integer_sequence<int, 32>{});
-      const bool mine = lane < ROWS && c0 + u < C;
-      const int unit = static_cast<int>(c0 + u) * kUnitBytes, ri = r0 + lane;
-      __builtin_amdgcn_raw_buffer_store_b128(u32x4{d[0], d[1], d[2], d[3]}, ro,
-                                             mine ? unit + 16 * ri : kPastRange, 0, 0);
-      __builtin_amdgcn_raw_buffer_store_b32(d[4], ro,
-                                            mine ? unit + kHeadBytes + 4 * ri : kPastRange, 0, 0);
+    for (int i = 0; i < kTpRound / WAVES; ++i) pack(buf, wave + i * WAVES, c0 + wave + i * WAVES);
+  }
+  // the units of a last round that is not whole, and no more (14336 x 128: 10.8 ->
+  // 5.4 us, x 1152 18.2 -> 13.2)
+  if (c0 < C) {
+#pragma unroll
+    for (int u = 0; u < kTpRound; ++u) {
+      if (c0 + u >= C) break;
+      codes[buf][u][rl][j] = static_cast<uint8_t>(tp_block(v[u], kept));
     }
+    tp_lds_barrier();
+#pragma unroll 1
+    for (int u = wave; c0 + u < C; u += WAVES) pack(buf, u, c0 + u);
   }
   part[rl][j] = kept;
   __syncthreads();
@@ -167,7 +179,12 @@ int launch_ternarize_pack(const float* w, int64_t n, int64_t k, uint8_t* out, fl
   // 17.9 / 19.5); 8 where it would leave CUs with one more than others, or
   // more than two per CU (6000 x 6000 35.8 / 33.2, 9000 x 4096 41.8 / 35.3, 14336 x 4096
   // 55.9 / 50.0, 16384 x 4096 62.8 / 55.7); 4 for matrices with few tiles, so
-  // that there are enough workgroups to spread over the GPU.
+  // that there are enough workgroups to spread over the GPU.  (The 8- and 4-row
+  // workgroups hold two and four rows of codes at once while they pack, 147
+  // registers against 71; packing one at a time, 78 registers, 1024 x 14336 takes
+  // 23.5 us instead of 21.8 and larger matrices the same.  The fourth workgroup of
+  // a CU has to wait then: 6206 x 14336 79 us, with 16 rows 75, at 4096 and 8192
+  // columns 22 and 47 against 24 and 56.)
   const int64_t per_cu = ceil_div(4 * R, 256);
   if (R >= 64 && per_cu <= 2 && 4 * R >= per_cu * 240)
     return launch(ternarize_pack_kernel<16>, dim3(static_cast<unsigned>(4 * R)), dim3(512), 0, s,
