@@ -675,17 +675,6 @@ __device__ __forceinline__ void fill_lut(uint32_t* lut) {
   if (threadIdx.x < 32) lut[threadIdx.x] = decode_word(threadIdx.x);
 }
 
-// Block of a grouped launch that workgroup b runs.  Workgroups are dispatched
-// to the 8 XCDs in turn (b -> XCD b % 8), each with its own L2; XCD x takes
-// the x-th contiguous eighth of the blocks, so that the workgroups of one
-// product meet in few L2s and its activation row is fetched there once.
-__device__ __forceinline__ int32_t xcd_block(int32_t b, int32_t grid) {
-  constexpr int32_t kXcds = 8;
-  const int32_t q = grid / kXcds, r = grid % kXcds;
-  const int32_t x = b % kXcds, slot = b / kXcds;
-  return x < r ? x * (q + 1) + slot : r * (q + 1) + (x - r) * q + slot;
-}
-
 // A grouped launch too small to fill the GPU runs 2^fold workgroups per
 // prepared block (launch_fold).  Workgroup sub of them takes an equal part of
 // the block's tiles, each split over 2^fold times as many waves (at most

@@ -577,13 +577,20 @@ __device__ __forceinline__ void wd_tokens(WdProblem& p, int64_t t0) {
   p.m = (p.m - t0 < G::TOK) ? static_cast<int>(p.m - t0) : G::TOK;
 }
 
-// grid: x = groups of TILES tiles, y = token blocks
+// grid: x = groups of TILES tiles, y = token blocks (wide_xcd_order: in eighths)
 template <class G>
 __global__ __launch_bounds__(G::THREADS) __attribute__((amdgpu_waves_per_eu(G::EU))) void wide_kernel(
     WdProblem p) {
   __shared__ __attribute__((aligned(16))) int8_t lds[G::LDS];
-  wd_tokens<G>(p, int64_t(blockIdx.y) * G::TOK);
-  wd_block<G>(p, blockIdx.x, lds);
+  const int groups = static_cast<int>(gridDim.x);
+  int g = blockIdx.x, tb = blockIdx.y;
+  if (wide_xcd_order(groups * G::TILES)) {
+    const int b = xcd_block(tb * groups + g, groups * static_cast<int>(gridDim.y));
+    tb = b / groups;
+    g = b - tb * groups;
+  }
+  wd_tokens<G>(p, int64_t(tb) * G::TOK);
+  wd_block<G>(p, g, lds);
 }
 
 // Grouped launch of 8 x 64 blocks, PER workgroups each (wide_run64).

@@ -83,6 +83,9 @@ int main() {
       std::printf("%d\n", a[1] <= kSmFoldBlocks && sm_splits(a[0], a[1], a[2] != 0) ? 1 : 0);
     } else if (fn == "sm_whole_sub") {
       std::printf("%d\n", sm_whole_sub(static_cast<int>(a[0])));
+    } else if (fn == "xcd_block") {
+      for (int b = 0; b < a[0]; ++b) std::printf("%d ", xcd_block(b, static_cast<int>(a[0])));
+      std::printf("\n");
     } else if (fn == "wide_pick") {
       std::printf("%d\n", wide_pick(a[0], a[1], a[2]));
     } else if (fn == "wide_pick_group") {

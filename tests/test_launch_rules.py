@@ -42,6 +42,15 @@ def test_whole_rows_spread_over_the_gpu():
     assert len(set(places)) == 32 and max(map(places.count, set(places))) <= 2 * 256 // 32
 
 
+def test_xcd_order_is_a_permutation_in_eighths():
+    for grid in (1, 7, 8, 9, 64, 203):
+        blocks, = ask(("xcd_block", grid))
+        assert sorted(blocks) == list(range(grid))
+        for x in range(min(8, grid)):  # an XCD's blocks are neighbours, in order
+            mine = blocks[x::8]
+            assert mine == list(range(mine[0], mine[0] + len(mine)))
+
+
 # blocks of a grouped launch, shape, workgroups per block, and the most tile
 # groups that one workgroup may run in series
 LAUNCHES = [(64, LONG, 1, 2), (64, MID, 2, 1), (64, HALF, 4, 1), (64, SHORT, 16, 1),
