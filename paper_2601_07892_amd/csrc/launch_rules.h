@@ -62,33 +62,38 @@ constexpr int sm_whole_sub(int block) {
 enum WideShape : int {
   kWideLong, kWideMid, kWideHalf, kWideQuarter, kWideShort, kWideTiny, kWidePair, kWideThin
 };
-// Estimated time (us) of a launch: the busiest CU runs c workgroups of U units
-// per wave; a lone workgroup takes fix + lat U, bound by one wave's chain, and c
-// of them base + c (thr U + o).  Fitted to measured launches (m 37-8192, n
-// 300-14336, k 128-14336), which it orders right or within 5% of the best.
+// Estimated time (us) of a lone launch: the busiest CU runs c workgroups of U
+// units per wave; a lone workgroup takes fix + lat U, bound by one wave's chain,
+// and c of them base + c (thr U + o).  Fitted to 1378 measured products (1049 with
+// per-group scales) of 5-16384 tokens, 64-14336 rows, 128-14336 weights a row, every
+// shape timed on each.  On 689 (526) others its choice takes 1.004 (1.006) times
+// the best shape's time on average, at most 1.19 (1.28).  (The constants before,
+// fitted to fewer and larger products: 1.022 and 1.036, at most 1.29 and 1.49, and
+// a few slower than on the kernel before these shapes: 261 x 10556 x 14208 63.8 ->
+// 69.2 us.)
 struct WideCost {
   int tokens, tiles, parts;
   float fix, lat, base, thr, o;
 };
 constexpr WideCost kWideCost[] = {
-    {128, 4, 1, 8.2f, 0.68f, 5.0f, 0.64f, 7.7f},   // long
-    {64, 4, 1, 6.0f, 0.54f, 5.0f, 0.45f, 1.7f},    // mid
-    {64, 2, 2, 6.0f, 0.575f, 5.0f, 0.50f, 2.0f},   // half
-    {64, 2, 4, 7.5f, 0.83f, 5.0f, 0.80f, 5.2f},    // quarter (eight waves)
-    {32, 1, 4, 5.0f, 0.55f, 4.0f, 0.41f, 1.1f},    // short
-    {32, 1, 8, 5.3f, 0.83f, 4.0f, 0.78f, 3.06f},   // tiny (eight waves)
-    {32, 2, 2, 5.0f, 0.55f, 4.0f, 0.50f, 1.1f},    // pair (grouped launches)
-    {32, 4, 1, 5.5f, 0.46f, 4.0f, 0.46f, 1.5f},    // thin (grouped launches)
+    {128, 4, 1, 9.127f, 0.68f, 5.442f, 0.558f, 3.541f},  // long
+    {64, 4, 1, 6.417f, 0.651f, 3.916f, 0.368f, 2.424f},  // mid
+    {64, 2, 2, 6.996f, 0.674f, 4.575f, 0.50f, 1.799f},   // half
+    {64, 2, 4, 7.5f, 0.83f, 4.324f, 0.882f, 5.2f},       // quarter (eight waves)
+    {32, 1, 4, 5.0f, 0.55f, 4.453f, 0.41f, 1.1f},        // short
+    {32, 1, 8, 5.3f, 0.83f, 3.095f, 0.78f, 2.55f},       // tiny (eight waves)
+    {32, 2, 2, 0, 0, 0, 0, 0},                           // pair (grouped launches)
+    {32, 4, 1, 0, 0, 0, 0, 0},                           // thin (grouped launches)
 };
 // The shapes with per-group scales (long, quarter and thin are not offered).
 constexpr WideCost kWideGroupCost[] = {
     {},
-    {64, 4, 1, 5.9f, 0.77f, 4.0f, 0.625f, 3.9f},   // mid
-    {64, 2, 2, 5.8f, 0.83f, 4.0f, 0.78f, 1.2f},    // half
+    {64, 4, 1, 4.905f, 0.952f, 2.233f, 0.604f, 2.635f},  // mid
+    {64, 2, 2, 5.863f, 0.80f, 4.047f, 0.701f, 1.483f},   // half
     {},
-    {32, 1, 4, 5.0f, 0.71f, 4.0f, 0.60f, 0.3f},    // short
-    {32, 1, 8, 5.6f, 1.07f, 4.0f, 1.05f, 3.1f},    // tiny (eight waves)
-    {32, 2, 2, 4.6f, 0.67f, 4.0f, 0.46f, 0.6f},    // pair
+    {32, 1, 4, 4.916f, 0.829f, 4.793f, 0.572f, 0.328f},  // short
+    {32, 1, 8, 5.6f, 1.07f, 3.616f, 0.971f, 3.216f},     // tiny (eight waves)
+    {32, 2, 2, 4.358f, 0.74f, 3.939f, 0.435f, 0.723f},   // pair
     {},
 };
 // `workgroups` of rows of `units` units; a part is whole chunks of `chunk` units.
@@ -143,24 +148,23 @@ constexpr int wide_batched_tokens(int max_m) { return max_m <= 32 ? 32 : 64; }
 // those, they give way.  Figures: mean time over the best shape's, products of one
 // length / mixed, about 100 launches each.
 //
-// 8 x 64 blocks.  By the cost model, at 24 units a row.  An odd last token block is
+// 8 x 64 blocks.  Up to 128 one round of the smaller shapes (33 .. 64: 64 x 2 1.00 /
+// 1.45, 32 x 1 1.30 / 1.01; 65 .. 128: 64 x 4 1.06 / 1.8, 64 x 2 1.05 / 1.15, but up to
+// 1.05 times the launch before these shapes; past that up to 1.3 times).  More: 64
+// x 4 or 128 x 4 by rounds of workgroups at 24 units a row, an odd last token block
 // priced for 128 x 4: one workgroup runs both halves of its tiles in series, 64
 // tokens of each idle (129 .. 256 blocks: 128 x 4 1.53 / 2.9 with an odd one, 1.03 /
-// 1.75 without; 64 x 4 1.00 / 1.5 and 1.03 / 1.45).  64 x 2 only up to 128 blocks
-// (past that up to 1.3 times the launch before these shapes).
+// 1.75 without; 64 x 4 1.00 / 1.5 and 1.03 / 1.45).
+constexpr WideCost kGroupedLong{128, 4, 1, 8.2f, 0.68f, 5.0f, 0.64f, 7.7f};
+constexpr WideCost kGroupedMid{64, 4, 1, 6.0f, 0.54f, 5.0f, 0.45f, 1.7f};
 constexpr int64_t kWideUnits = 24;
 constexpr int wide_pick_batched(int64_t total_blocks, int max_m) {
+  if (total_blocks <= 128) return total_blocks <= 32 ? kWideShort : total_blocks <= 64 ? kWideHalf : kWideMid;
   const int64_t tb = ceil_div(max_m, 64);
-  const WideCost& l = kWideCost[kWideLong];
-  WidePick q{};
-  q.offer(kWideLong, wide_estimate(l, ceil_div(total_blocks * ((tb + 1) / 2 * 2), tb), kWideUnits) +
-                         (tb % 2 ? l.lat * kWideUnits : 0.0f));
-  q.offer(kWideMid, wide_estimate(kWideCost[kWideMid], 2 * total_blocks, kWideUnits));
-  if (total_blocks <= 128) {
-    q.offer(kWideHalf, wide_estimate(kWideCost[kWideHalf], 4 * total_blocks, kWideUnits));
-    q.offer(kWideShort, wide_estimate(kWideCost[kWideShort], 16 * total_blocks, kWideUnits));
-  }
-  return q.best;
+  const float longs =
+      wide_estimate(kGroupedLong, ceil_div(total_blocks * ((tb + 1) / 2 * 2), tb), kWideUnits) +
+      (tb % 2 ? kGroupedLong.lat * kWideUnits : 0.0f);
+  return longs <= wide_estimate(kGroupedMid, 2 * total_blocks, kWideUnits) ? kWideLong : kWideMid;
 }
 // 8 x 32 blocks.  65 .. 96: 32 x 1 1.18 / 1.00 (32 x 2 1.01 / 1.53); 97 .. 192: 32
 // x 2 1.02 / 1.5 (32 x 1 1.4 / 1.00, and slower than the launch before these

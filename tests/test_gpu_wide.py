@@ -36,8 +36,9 @@ def _inputs(dev, m, n, k, tag):
     return t, q, sx, w, torch.from_numpy(q).to(dev), torch.from_numpy(sx).to(dev)
 
 
-# by the launch's cost model: 32 x 1 (K in 4), 32 x 1 (K in 8), 64 x 2 (K in
-# 2), 64 x 2 (K in 4), 64 x 4, 128 x 4; token, row and K remainders of each
+# the cost model's shapes, every one of which some case takes (checked on the CPU
+# beside the launch rules): 32 x 1 (K in 4), 32 x 1 (K in 8), 64 x 2 (K in 2), 64 x
+# 2 (K in 4), 64 x 4, 128 x 4; token, row and K remainders of each
 # (k % 128 and k % 16 of every kind, parts of K that are shorter or empty)
 LONE = [(5, 1, 4), (33, 65, 68), (70, 130, 1028), (300, 330, 644), (257, 1030, 1540), (31, 64, 384),
         (65, 70, 8196), (100, 130, 12292), (16, 3072, 3072),
@@ -137,7 +138,7 @@ def _group_ok(y, q, t, sx, gs, k):
 LONE_GROUP = [(5, 64, 128), (33, 70, 132), (37, 130, 1028), (31, 300, 516), (100, 70, 8196),
               (385, 8190, 132), (641, 5122, 388), (385, 8190, 1028), (17, 66, 4),
               (5, 70, 512), (65, 130, 2044), (40, 300, 3584), (33, 580, 8192), (513, 2900, 2044),
-              (385, 5122, 508), (257, 8190, 512)]
+              (385, 5122, 508), (257, 8190, 512), (226, 4100, 1540)]
 
 
 @pytest.mark.parametrize("m,n,k", LONE_GROUP)
