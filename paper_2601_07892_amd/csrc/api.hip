@@ -39,9 +39,10 @@ int check_fused(const uint8_t* w, const float* x, const float* x_scale, float* y
   return SHERRY_OK;
 }
 
-// Largest M the VALU decode kernel serves: up to 4 tokens it is faster than
-// the register-decoded MFMA kernel (LLaMA-3.2-3B and 8B-scale projections,
-// single launches).
+// Largest M the VALU decode kernel serves.  Single launches, VALU against
+// register-decoded MFMA kernel, us: 3072 x 3072 4.0 / 6.8 at one token, 5.9 / 6.8 at
+// four; 3072 x 8192 6.5 / 10.5 and 10.9 / 10.5; 14336 x 4096 5.1 / 8.1 and 7.6 / 8.2;
+// 4096 x 14336 9.4 / 14.9 and 16.9 / 15.0.
 constexpr int64_t kGemvMaxM = 4;
 // Past that, products of more than kTiledMinM tokens with k <= n and k <=
 // kTiledMaxK run on the LDS-tiled kernel, all others on the register-decoded

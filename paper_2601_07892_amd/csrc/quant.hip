@@ -7,12 +7,13 @@
 // for longer ones (quant_shape).  Rows up to 32768 values are read once into
 // registers; longer rows are read twice (absmax, then quantize).
 //
-// What bounds it: launch and memory latency at decode sizes, HBM at prefill
-// sizes.  A thread's loads go out back to back (the row's end through the
-// range of a buffer resource, not a branch per load), and quant4 takes about 6
-// VALU operations per value (15 before, 2-6 us of a 2048-token launch):
-// 2048 x 14336 32.3 -> 26.9 us (5.5 TB/s), 8192 x 4096 32.9 -> 29.2,
-// 2048 x 3072 8.8 -> 7.9, 64 x 14336 6.8 -> 5.9, 1000 x 30000 51.7 -> 28.7.
+// What bounds it: launch and memory latency at decode sizes, HBM (or the
+// Infinity Cache, where the kernel before left the row there) at prefill sizes.
+// A thread's loads go out back to back (the row's end through the range of a
+// buffer resource, not a branch per load), and quant4 takes about 6 VALU
+// operations per value (15 before).  Inputs out of cache, against the branches and
+// 15 operations: 2048 x 14336 31.5 -> 25.8 us, 8192 x 4096 32.6 -> 28.4, 2048 x 3072
+// 8.6 -> 8.1, 64 x 14336 6.1 -> 4.5 (in cache), 1000 x 30000 51.6 -> 28.2.
 #include <type_traits>
 
 #include "sherry_internal.h"
