@@ -30,8 +30,8 @@
 // Shorter products are bound by one wave's chain (a container takes a lone
 // wave about 0.55 us, mostly instruction issue: deeper rings of weights or
 // stages changed nothing) and by about 5 us of launch, first loads, reduction
-// and stores.  They run smaller workgroups with K split over more waves, as
-// the cost model below picks.
+// and stores.  They run smaller workgroups with K split over more waves
+// (wide_pick*, launch_rules.h).
 #include <type_traits>
 
 #include "sherry_internal.h"
