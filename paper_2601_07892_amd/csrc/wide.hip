@@ -1,6 +1,7 @@
-// Register-decoded int8-MFMA product (Eq. 2): every lone product of five and
-// more tokens, and the grouped launches of more than 16 (with per-group scales
-// whose rows the window kernel does not take, of more than four).
+// Register-decoded int8-MFMA product (Eq. 2): the lone products of five and more
+// tokens (but for long ones of short rows, sherry_gemm_kernel_for), and the
+// grouped launches of more than 16 (with per-group scales whose rows the window
+// kernel does not take, of more than four).
 //
 // Work mapping.  A wave owns one 64-row tile (or one of S parts of its K) and
 // 32 MT tokens; a workgroup is W waves, W / S tiles.  Per container (64 rows x
